@@ -30,7 +30,7 @@ def listed():
     return [
         # a first look at a small particle: the latency of every launch and host wait of the chain
         {"name": "reconstruct_16", "op": "reconstruct", "N": 16, "M": 200, "views": "haar", "groups": 0, "shifts": False,
-         "W": 7, "iters": 8},
+         "W": 7, "iters": 4},
         # the kernel of the mid workload; the preconditioner's training builds thousands of these
         {"name": "kernel_64", "op": "kernel", "N": 64, "M": 10000, "views": "haar", "groups": 10, "W": 7},
         # the kernel of the headline workload: once per reconstruction, its largest part with A*b
@@ -95,7 +95,7 @@ def draw(rng):
     if op == "train":
         return {"op": op, "N": 64, "batch": rng.randint(1, 8), "k": rng.randint(8, 32)}
     return {"op": op, "N": rng.choice([8, 16, 32]), "M": _log_int(rng, 50, 2000), "views": rng.choice(["haar", "vmf"]),
-            "groups": rng.choice([0, 3]), "shifts": rng.random() < 0.5, "W": 7, "iters": rng.randint(3, 8)}
+            "groups": rng.choice([0, 3]), "shifts": rng.random() < 0.5, "W": 7, "iters": rng.randint(2, 4)}
 
 
 # ------------------------------------------------------------------ inputs --
