@@ -84,10 +84,13 @@ void solve_dense(std::vector<double>& A, std::vector<double>& y, int n) {
 // the cell offset is u = f - W/2 + j) interpolating phi at Chebyshev nodes; reciprocal
 // transforms for the deconvolution of the kernel (L = 4N, circulant positions) and of
 // A*b (L = 2N, centred indices).
+// The window is even, so the polynomials of cells j and W-1-j mirror each other: kb_sym holds, per
+// pair, the even powers' coefficients of cell j (6) and then the odd powers' (5).
 void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, std::vector<float>& datb) {
     const int W = p->kbw, D = KB_DEG, N = p->N;
     const double beta = p->beta;
     poly.assign((size_t)W * (D + 1), 0.f);
+    std::vector<double> coef((size_t)W * (D + 1));
     for (int j = 0; j < W; ++j) {
         std::vector<double> A((D + 1) * (D + 1)), y(D + 1);
         for (int i = 0; i <= D; ++i) {
@@ -98,8 +101,17 @@ void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, 
             y[i] = kb_phi(u, W, beta);
         }
         solve_dense(A, y, D + 1);
-        for (int k = 0; k <= D; ++k) poly[j * (D + 1) + k] = (float)y[k];
+        for (int k = 0; k <= D; ++k) {
+            coef[j * (D + 1) + k] = y[k];
+            poly[j * (D + 1) + k] = (float)y[k];
+        }
     }
+    const int NE = D / 2 + 1;
+    for (int j = 0; j < (W + 1) / 2; ++j)
+        for (int k = 0; k <= D; ++k) {
+            const double a = coef[j * (D + 1) + k], b = coef[(W - 1 - j) * (D + 1) + k];
+            p->kb_sym[j * (D + 1) + (k % 2 ? NE + k / 2 : k / 2)] = (float)(0.5 * (k % 2 ? a - b : a + b));
+        }
     dker.assign(2 * N, 0.f);
     const double Lk = 4.0 * N;
     for (int pp = 0; pp < 2 * N; ++pp) {
@@ -146,7 +158,7 @@ void firm_plan_destroy(firm_plan p) {
                    p->tiles_ker, p->tiles_atb, p->dscal, p->rowstart, p->flags, p->khat64, p->T1d,
                    p->T2d, p->tw64, p->x64, p->r64, p->p64, p->q64, p->y64, p->atb64, p->rhs, p->dvec,
                    p->img_ws, p->khat16, p->shtab, p->uws, p->usc, p->c12s, p->nrms, p->groups, p->shiftss,
-                   p->vorder, p->vbox};
+                   p->vorder, p->vbox, p->vrec, p->rbox, p->tiles_prj};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     if (p->host_scal) (void)hipHostFree(p->host_scal);
@@ -248,6 +260,8 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     std::vector<double> shs(shifts ? (size_t)M * 2 : 0);
     const int nvblk = (M + SP_VBLK - 1) / SP_VBLK;
     std::vector<float4> vbox((size_t)nvblk * 2);
+    const int nrun = (M + SP_VRUN - 1) / SP_VRUN;
+    std::vector<float4> vrec((size_t)M * 2), rbox((size_t)nrun * 2);
     {
         std::vector<std::pair<uint64_t, int32_t>> key(M);
         for (int m = 0; m < M; ++m) {
@@ -276,7 +290,21 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
             for (int d = 0; d < 3; ++d) nrms[4 * (size_t)j + d] = sg * n[d];
             nrms[4 * (size_t)j + 3] = 0.f;
             grps[j] = grp[m];
+            const double* c = &c12[6 * (size_t)m];
+            auto bits = [](int32_t i) { float f; std::memcpy(&f, &i, 4); return f; };
+            vrec[2 * (size_t)j] = make_float4((float)c[0], (float)c[1], (float)c[2], (float)c[3]);
+            vrec[2 * (size_t)j + 1] = make_float4((float)c[4], (float)c[5], bits(grp[m]), bits(m));
             if (shifts) { shs[2 * (size_t)j] = shifts[2 * (size_t)m]; shs[2 * (size_t)j + 1] = shifts[2 * (size_t)m + 1]; }
+        }
+        for (int r = 0; r < nrun; ++r) {
+            float lo[3] = {1e30f, 1e30f, 1e30f}, hi[3] = {-1e30f, -1e30f, -1e30f};
+            for (int j = r * SP_VRUN; j < std::min(M, (r + 1) * SP_VRUN); ++j)
+                for (int d = 0; d < 3; ++d) {
+                    lo[d] = std::min(lo[d], nrms[4 * (size_t)j + d]);
+                    hi[d] = std::max(hi[d], nrms[4 * (size_t)j + d]);
+                }
+            rbox[2 * (size_t)r] = make_float4(lo[0], lo[1], lo[2], 0.f);
+            rbox[2 * (size_t)r + 1] = make_float4(hi[0], hi[1], hi[2], 0.f);
         }
         for (int bk = 0; bk < nvblk; ++bk) {
             float lo[3] = {1e30f, 1e30f, 1e30f}, hi[3] = {-1e30f, -1e30f, -1e30f};
@@ -329,10 +357,12 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
         e = std::min(std::max(e, -100), 100);
         p->fx_ker = std::ldexp(1.0f, e);
     }
-    std::vector<int> wk = spread_worklist(4 * N, spread_tile_real(), M, 4.0);
-    std::vector<int> wa = spread_worklist(2 * N, spread_tile_cplx(), M, 2.0);
+    std::vector<int> wk = spread_points_worklist(N, p->kbw, M, false);
+    std::vector<int> wa = spread_points_worklist(N, p->kbw, M, true);
+    std::vector<int> wp = spread_worklist(2 * N, TileDims{PJ_TILE, PJ_TILE, PJ_TILE}, 2 * N - 1, 0.0, M, SP_VBLK);
     p->ntiles_ker = (int)(wk.size() / 4);
     p->ntiles_atb = (int)(wa.size() / 4);
+    p->ntiles_prj = (int)(wp.size() / 4);
 
     const int64_t n3 = (int64_t)N * N * N;
     const int64_t N2 = 2 * N;
@@ -349,6 +379,8 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     if (shifts) chk(dalloc(&p->shiftss, (size_t)M * 2));
     chk(dalloc(&p->vorder, (size_t)M));
     chk(dalloc(&p->vbox, vbox.size()));
+    chk(dalloc(&p->vrec, vrec.size()));
+    chk(dalloc(&p->rbox, rbox.size()));
     chk(dalloc(&p->kb_poly, poly.size()));
     chk(dalloc(&p->deconv_ker, dker.size()));
     chk(dalloc(&p->deconv_atb, datb.size()));
@@ -375,9 +407,17 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     chk(dalloc(&p->S1, (size_t)((int64_t)N * N * p->QPn)));
     chk(dalloc(&p->dscal, 8));
     p->fx_bmax = reinterpret_cast<unsigned*>(p->dscal + 1);
+    p->taken = reinterpret_cast<int*>(p->dscal + 2);
+    {
+        int dev = 0, n = 0;
+        chk(hipGetDevice(&dev));
+        chk(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        if (n > 0) p->ncu = n;
+    }
     chk(dalloc(&p->rowstart, (size_t)(N + 1)));
     chk(dalloc(&p->tiles_ker, wk.size()));
     chk(dalloc(&p->tiles_atb, wa.size()));
+    chk(dalloc(&p->tiles_prj, wp.size()));
     if (e == hipSuccess) e = hipHostMalloc((void**)&p->host_scal, 32 * sizeof(double), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc((void**)&p->host_flags, 8 * sizeof(int), hipHostMallocDefault);
     if (e != hipSuccess) {
@@ -399,6 +439,8 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     if (shifts) up(p->shiftss, shs.data(), shs.size() * sizeof(double));
     up(p->vorder, vord.data(), vord.size() * sizeof(int32_t));
     up(p->vbox, vbox.data(), vbox.size() * sizeof(float4));
+    up(p->vrec, vrec.data(), vrec.size() * sizeof(float4));
+    up(p->rbox, rbox.data(), rbox.size() * sizeof(float4));
     up(p->kb_poly, poly.data(), poly.size() * sizeof(float));
     up(p->deconv_ker, dker.data(), dker.size() * sizeof(float));
     up(p->deconv_atb, datb.data(), datb.size() * sizeof(float));
@@ -406,6 +448,7 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     up(p->rowstart, rowstart.data(), rowstart.size() * sizeof(int));
     up(p->tiles_ker, wk.data(), wk.size() * sizeof(int));
     up(p->tiles_atb, wa.data(), wa.size() * sizeof(int));
+    up(p->tiles_prj, wp.data(), wp.size() * sizeof(int));
     if (e == hipSuccess) e = noalloc_scratch_setup();
     if (e != hipSuccess) {
         firm_plan_destroy(p);

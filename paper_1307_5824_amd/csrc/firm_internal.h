@@ -44,12 +44,17 @@ struct firm_plan_s {
     double* shiftss = nullptr;
     int32_t* vorder = nullptr;  // gridding position -> view index
     float4* vbox = nullptr;     // 2 per block: (min n, max |n|_1), (max n, 0)
+    float4* vrec = nullptr;     // 2 per view: (c1, c2x), (c2y, c2z, group, caller's view), in FP32
+    float4* rbox = nullptr;     // 2 per run of SP_VRUN views: (min n, 0), (max n, 0)
     double ker_k0 = 0.0;       // sum_m h_m(0)^2: the k = 0 term of Ker
 
     // Kaiser-Bessel window (device)
     float* kb_poly = nullptr;  // w x (KB_DEG+1) polynomial coefficients on f in [0, 1]
+    float kb_sym[44] = {};     // the same by pairs of cells, split into even and odd powers of 2 f - 1 (host)
     float fx_ker = 1.f;        // kernel gridding: integer units per unit (power of 2, terms < 2^31)
     float fx_atb_coef = 0.f;   // A*b gridding: units per unit times the largest |b component| may reach
+    int* taken = nullptr;      // device word: work items handed out by the running gridding kernel (inside dscal)
+    int ncu = 256;             // compute units of the plan's device
     unsigned* fx_bmax = nullptr;  // device word: bits of the largest |b component| (inside dscal)
     float* deconv_ker = nullptr;  // 2N: 1/phihat at circulant position p (L = 4N)
     float* deconv_atb = nullptr;  // N: 1/phihat at centred index i (L = 2N)
@@ -95,6 +100,7 @@ struct firm_plan_s {
     void* ws2 = nullptr; size_t ws2_bytes = 0;
     int* tiles_ker = nullptr; int ntiles_ker = 0;   // work list for the kernel spread
     int* tiles_atb = nullptr; int ntiles_atb = 0;   // work list for the A*b spread
+    int* tiles_prj = nullptr; int ntiles_prj = 0;   // work list for the forward projector
     double* dscal = nullptr;   // small device scratch for the A*b k=0 term
     int* rowstart = nullptr;   // N+1: disk index of (k1, 0), so idx(k1, k2) = rowstart[k1 + N/2] + k2
     int* flags = nullptr;      // CG control words on device (see cg.hip)
@@ -207,9 +213,11 @@ firm_status cg_solve64(firm_plan p, const double* atb, double* x, double lam, do
                        const float* d, firm_cg_report* rep);
 hipError_t precond_set(firm_plan p, const float* d_centred);
 
-std::vector<int> spread_worklist(int L, int T, int M, double s);
-int spread_tile_real();
-int spread_tile_cplx();
+struct TileDims { int t0, t1, t2; };
+std::vector<int> spread_worklist(int L, TileDims T, int last, double shift, int M, int gran);
+std::vector<int> spread_points_worklist(int N, int W, int M, bool cplx);
+constexpr int PJ_TILE = 12;   // the forward projector's tile edge
+constexpr int SP_VRUN = 64;   // views per run of the gridding's view order (one wavefront's)
 constexpr int SP_VBLK = 512;  // views per block of the gridding's view order (its workgroup size)
 void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, std::vector<float>& datb);
 

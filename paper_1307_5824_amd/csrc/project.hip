@@ -22,7 +22,6 @@
 #include "firm_internal.h"
 
 #define KB_DEG 10
-#define PJ_TILE 12
 #define PJ_QCAP 2048
 #define PJ_THREADS 512
 #define PJ_PREP_BLOCKS 1024
@@ -414,7 +413,6 @@ __global__ void __launch_bounds__(NTH, (W <= 7 ? 4 : 2)) k_project(ProjArgs a) {
 // Workspaces: p->tmp (u), p->T1, p->ws1, p->grid (the caller has sized the gridding workspaces).
 hipError_t forward_project(firm_plan p, const float* V, float2* b) {
     const int N = p->N, L = 2 * N;
-    if (spread_tile_cplx() != PJ_TILE) return hipErrorInvalidValue;
     hipStream_t st = p->stream;
     const int nblk = std::min<int>(PJ_PREP_BLOCKS, p->npart);
     hipLaunchKernelGGL(k_fp_prep, dim3(nblk), dim3(256), 0, st, V, p->deconv_atb, N, p->tmp, p->partials);
@@ -425,7 +423,7 @@ hipError_t forward_project(firm_plan p, const float* V, float2* b) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
     float2* X = reinterpret_cast<float2*>(p->grid);
     if ((e = fft_project_grid(p, p->tmp, p->T1, reinterpret_cast<float2*>(p->ws1), X)) != hipSuccess) return e;
-    if (p->ntiles_atb == 0) return hipSuccess;
+    if (p->ntiles_prj == 0) return hipSuccess;
     ProjArgs a;
     a.N = N; a.M = p->M; a.L = L; a.nt = (L + PJ_TILE - 1) / PJ_TILE; a.P = p->P; a.Q = p->Q; a.QP = p->QP;
     a.s = 2.0;
@@ -433,9 +431,9 @@ hipError_t forward_project(firm_plan p, const float* V, float2* b) {
     static_assert(PJ_THREADS == SP_VBLK, "a block of views per round and thread");
     a.c12 = p->c12s; a.nrm = p->nrms; a.group = p->groups; a.table = p->table; a.poly = p->kb_poly;
     a.vorder = p->vorder; a.vbox = p->vbox;
-    a.work = reinterpret_cast<const int4*>(p->tiles_atb);
+    a.work = reinterpret_cast<const int4*>(p->tiles_prj);
     a.X = X; a.shifts = p->shiftss; a.rowstart = p->rowstart; a.b = b;
-    const dim3 grid(p->ntiles_atb), blk(PJ_THREADS);
+    const dim3 grid(p->ntiles_prj), blk(PJ_THREADS);
     switch (p->kbw) {
         case 4: hipLaunchKernelGGL((k_project<PJ_TILE, 4, PJ_THREADS>), grid, blk, 0, st, a); break;
         case 5: hipLaunchKernelGGL((k_project<PJ_TILE, 5, PJ_THREADS>), grid, blk, 0, st, a); break;

@@ -6,49 +6,38 @@
 // Each point is spread with a separable Kaiser-Bessel window of width W onto a
 // periodic grid; a grid FFT divided by the window's transform gives the sums.
 //
-// Work decomposition: the grid is cut into T^3 tiles.  A workgroup owns one
-// tile (or one tile and a range of images): it tests every image plane of its
-// range against the tile's cube, enumerates the disk points of the surviving
-// images whose cell floor(t + L/2) lies in the tile (an exact k2 interval per
-// row), and accumulates their full W^3 stencils into a (T + W)^3 LDS tile; the
-// tile is then added to the global grid with one atomic per cell.  Each point is
-// spread exactly once.
+// A workgroup owns one tile of window starts (or one tile and a range of views):
+// points.h finds its points and sorts them into bins, and a wavefront sums a chunk
+// of one bin's points as a matrix product on the matrix units: the chunk's 16 x CJ x 8
+// cells are W0^T (points x 16 rows) times W1 W2 (points x CJ 8 columns), four points per
+// instruction.  The chunk's FP32 sums (at most PT_CHUNK terms) then go to the
+// workgroup's LDS tile as 64-bit integers, one atomic per cell and chunk, where one
+// per cell and point was needed without the matrix units; the tile is added to the
+// global grid at the end with one atomic per nonzero cell.  Each point is spread
+// exactly once.
 //
 // LDS float atomics run at a small fraction of the plain read/write rate on this
 // chip, 64-bit integer atomics at about the plain rate.  The tile is therefore
-// accumulated in fixed point: 64-bit integer cells, each term the FP32 product
-// rounded to an integer in units of 1/fxs (a power of 2 with |term| < 2^31),
-// added with one integer atomic per cell.  Integer sums are exact and independent
-// of the order of the adds, so every wavefront takes any staged point.  The
-// per-point window weights are computed once, one thread per point and axis, and
-// staged in LDS; the lanes of a wavefront sit on the W x W footprint of the last
-// two axes and add the point's W rows.  Ker's terms are non-negative; A*b is
-// spread one component (re, then im) per launch, with signed terms and a unit
-// that follows from the largest |component| of the data.  Only the half disk (k1 > 0, or k1 = 0 and
-// k2 > 0) is spread: its partner -k is folded in (Ker is real and even; for A*b
-// the pair (k, -k) gives the real part exactly), and k = 0 is added afterwards
-// in closed form.
+// accumulated in fixed point: 64-bit integer cells in units of 1/fxs (a power of 2
+// with |term| < 2^31).  Integer sums are exact and independent of the order of the
+// adds.  Ker's terms are non-negative; A*b's are signed, both components in one pass
+// over the points, with a unit that follows from the largest |component| of the data.
+// Only the half disk (k1 > 0, or k1 = 0 and k2 > 0) is spread: its partner -k is
+// folded in (Ker is real and even; for A*b the pair (k, -k) gives the real part
+// exactly), and k = 0 is added afterwards in closed form.
 #include <algorithm>
 #include <cmath>
 #include <vector>
 
 #include "firm_internal.h"
-
-#define KB_DEG 10
-#define SP_QCAP 1024
+#include "points.h"
 
 namespace {
 
 struct SpreadArgs {
-    int N, M, L, nt;
-    double s;
-    const double* c12;
-    const float* nrm;
-    const int32_t* group;
+    pts::Args p;
     const float* table;
     int Q;
-    const float* poly;
-    const int4* work;
     void* grid;
     const float2* b;
     const double* shifts;
@@ -60,127 +49,34 @@ struct SpreadArgs {
     // are at fx_bmax (the largest |component| of the data), found on the device before the launch
     const unsigned* fx_bmax;
     float fx_coef;
-    int comp;  // complex data spread one component at a time: the component (0 re, 1 im)
-    // the per-view arrays above are in the gridding's view order; vorder maps a position to the
-    // caller's view index (for b), vbox holds per block of SP_VBLK views the box of the normals
-    const int* vorder;
-    const float4* vbox;
 };
 
-template <int W>
-__device__ __forceinline__ void kb_weights(const float* __restrict__ poly, float x, float* out) {
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        const float* c = poly + j * (KB_DEG + 1);
-        float v = c[KB_DEG];
-#pragma unroll
-        for (int d = KB_DEG - 1; d >= 0; --d) v = fmaf(v, x, c[d]);
-        out[j] = v;
-    }
+// Tiles: the kernel's 10 x 16 x 16 starts (W = 7; 62 KB of 64-bit cells, 64 bins, grid 4N), A*b's
+// 10 x 10 x 12 with two components per cell (74 KB, 30 bins, grid 2N, where a view leaves four
+// times the points in a tile).
+template <int W, bool CPLX>
+using SpreadTile = pts::Tile<W, (CPLX ? 2 : 4), 1, (CPLX ? 16 : 22), (CPLX ? 18 : 22), (CPLX ? 16 : 8), (CPLX ? 2 : 1)>;
+
+// The integer nearest to x (|x| < 2^51), by the FP64 sum whose last place is one.
+__device__ __forceinline__ unsigned long long to_units(float x) {
+    return (unsigned long long)__double_as_longlong((double)x + 6755399441055744.0) - 0x4338000000000000ull;
 }
 
-// LDS bank layout of the footprint accesses.  LDS has 32 banks of 4 bytes and serves a wave's
-// access in groups of lanes: two groups of 32 for 4-byte elements, four groups of 16 for
-// 8-byte elements (G groups of 64 / G lanes, whose elements must fall in 64 / G distinct
-// element slots modulo 128 bytes).  The W x W footprint cells j2 * pitch + j3 (in elements) are
-// split by rows among the G groups so that each group's cells are conflict-free.
-// place_rows: assign rows r.. to groups (grp[]), by backtracking.
-constexpr bool place_rows(int r, int W, int rp, int G, int* grp) {
-    if (r == W) return true;
-    const int cap = 64 / G;
-    for (int g = 0; g < G; ++g) {
-        int n = 0;
-        for (int q = 0; q < r; ++q) n += grp[q] == g;
-        if ((n + 1) * W > cap) continue;
-        bool ok = true;
-        for (int q = 0; q < r && ok; ++q) {
-            if (grp[q] != g) continue;
-            for (int i = 0; i < W && ok; ++i)
-                for (int j = 0; j < W && ok; ++j)
-                    if ((q * rp + i) % cap == (r * rp + j) % cap) ok = false;
-        }
-        if (!ok) continue;
-        grp[r] = g;
-        if (place_rows(r + 1, W, rp, G, grp)) return true;
-    }
-    return false;
+// A point's value in fixed-point units: every term stays below 2^31 for finite data; NaN counts as
+// zero and infinities as 2^32, so that no other point of the bin is touched.
+__device__ __forceinline__ float bounded(float v) {
+    return v == v ? fminf(fmaxf(v, -4294967296.f), 4294967296.f) : 0.f;
 }
 
-// group of every footprint row (two bits per row) for row pitch rp, or -1 if none is
-// conflict-free
-constexpr int row_groups(int rp, int W, int G) {
-    int grp[8] = {};
-    if (!place_rows(0, W, rp, G, grp)) return -1;
-    int code = 0;
-    for (int r = 0; r < W; ++r) code |= grp[r] << (2 * r);
-    return code;
-}
+template <int W, bool CPLX>
+__global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs a) {
+    using T = SpreadTile<W, CPLX>;
+    constexpr int NC = CPLX ? 2 : 1, NJ = T::NJ;
+    __shared__ unsigned long long tile[NC][T::CELLS];
+    __shared__ pts::Lds<T> s;
+    __shared__ int rowstart[CPLX ? 132 : 1];  // the disk's rows k1 >= 0 (N <= 256)
 
-// smallest LDS row pitch >= PT that admits a conflict-free split
-constexpr int row_pitch(int PT, int W, int G) {
-    for (int rp = PT; rp < PT + 32; ++rp)
-        if (row_groups(rp, W, G) >= 0) return rp;
-    return PT;
-}
-
-// Fine-grid position of the disk point (k1, k2) of a view along axis d: the one expression
-// that both the point enumeration (which tile owns the point) and the staging (where its
-// window starts) evaluate, so that the two agree to the last bit.
-__device__ __forceinline__ double tau_of(double s, int k1, int k2, double cd, double c3d, double halfL) {
-    return fma(s, fma((double)k2, c3d, (double)k1 * cd), halfL);
-}
-
-// Points staged per batch: the most, in whole rounds (a round gives every wavefront FQ points),
-// that keep one staging item (point, axis) per thread and the workgroup's LDS within its budget.
-constexpr int sp_batch(int nth, int fixed_bytes, int per_point, int budget, int round) {
-    int pb = nth / 3 / round * round;
-    while (pb > round && fixed_bytes + pb * per_point > budget) pb -= round;
-    return pb;
-}
-
-// One tile plane of 64-bit integer cells.  Complex data (A*b) is spread one component per
-// launch (a.comp), so that its tile is as small as the kernel's: two workgroups per CU up to
-// W = 7, one for W = 8.
-template <int T, int W, bool CPLX, int NTH>
-__global__ void __launch_bounds__(NTH, (W >= 8 ? NTH / 256 : NTH / 128)) k_spread(SpreadArgs a) {
-    constexpr int SP_THREADS = NTH, SP_WAVES = NTH / 64;
-    constexpr int PT = T + W;
-    constexpr int PADLO = (W + 1) / 2 - 1;
-    constexpr int NCELL = PT * PT * PT;
-    constexpr int G = 4;                               // lane groups of an 8-byte LDS access
-    constexpr int RP = row_pitch(PT, W, G);            // LDS pitch of a tile row, in cells (conflict-free)
-    constexpr int GROUPS = row_groups(RP, W, G);       // lane group of every footprint row
-    constexpr int PP = PT * RP;                        // LDS pitch of a tile plane
-    // staged point: the W window weights of axes 0, 1, 2 at 0, W, 2W (axis 0 times the point's
-    // value in fixed-point units); stride in floats
-    constexpr int PSTR = 3 * W;
-    static_assert(W >= 3 && W <= 8, "window width");
-    constexpr int FQ = 4;  // points a wavefront accumulates at a time (see the accumulation)
-    // LDS besides the staged points: the tile, the view slots (and for complex data their views,
-    // groups and the disk's row starts), the queue, and 512 bytes for the counters, the tile
-    // constants, the lane map, the flush's partial sums and alignment.  The batch is as large as
-    // the rest allows: two workgroups share a CU up to W = 7 (80 KB each), one at W = 8.
-    // the queue: the A*b tile leaves room for 256 more entries (fewer stops of the enumeration);
-    // the kernel's tile 32 fewer, for the block mask of the culling
-    constexpr int QCAP = CPLX ? SP_QCAP + 256 : SP_QCAP - 32;
-    constexpr int LDS_FIXED = PT * PP * 8 + NTH * 4 * (CPLX ? 3 : 1) + (CPLX ? 264 * 4 : 0) + QCAP * 4 + 512;
-    constexpr int SP_PB = sp_batch(NTH, LDS_FIXED, PSTR * 4 + 4, W >= 8 ? 160 * 1024 : 80 * 1024, FQ * SP_WAVES);
-    static_assert(SP_PB >= FQ * SP_WAVES && 3 * SP_PB <= NTH, "staging batch");
-    constexpr int NIT = (3 * SP_PB + NTH - 1) / NTH;   // staging items (point, axis) per thread
-    __shared__ __align__(16) unsigned long long tile64[PT * PP];
-    __shared__ __align__(16) float pt_w[SP_PB * PSTR];
-    __shared__ int pt_lo[SP_PB];                       // window starts of axes 0, 1, 2 in bytes 0, 1, 2
-    __shared__ int img_m[SP_THREADS];
-    __shared__ int img_o[CPLX ? SP_THREADS : 1];  // complex data: the slot's view in the caller's order
-    __shared__ int img_g[CPLX ? SP_THREADS : 1];  // complex data: the slot's CTF group
-    __shared__ int rs_l[CPLX ? 264 : 1];              // row starts of the disk order (N <= 256)
-    __shared__ int queue[QCAP];
-    __shared__ int nimg, qn, qfail, any;
-    __shared__ float geo[12];  // the tile's constants (see below)
-    __shared__ unsigned short lmap[64];  // footprint cell of each lane (see below)
-
-    const int tid = threadIdx.x;
-    const int4 wk = a.work[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63;
     float fxs = a.fxs;
     double fx_inv = a.fx_inv;
     if (a.fx_bmax) {
@@ -190,419 +86,138 @@ __global__ void __launch_bounds__(NTH, (W >= 8 ? NTH / 256 : NTH / 128)) k_sprea
         fxs = ldexpf(1.f, e);
         fx_inv = ldexp(1.0, -e);
     }
-    const int nt = a.nt;
-    const int tt0 = wk.x / (nt * nt), tt1 = (wk.x / nt) % nt, tt2 = wk.x % nt;
-    const int L = a.L, N = a.N;
-    const double halfL = 0.5 * L;
-
-    for (int i = tid; i < PT * PP; i += SP_THREADS) tile64[i] = 0ull;
-    if (tid == 0) { any = 0; nimg = 0; qn = 0; qfail = QCAP; }
+    const int N = a.p.N;
+    const double inv_n = 1.0 / N;
     if constexpr (CPLX)
-        for (int i = tid; i <= a.N; i += SP_THREADS) rs_l[i] = a.rowstart[i];
+        for (int i = tid; i <= N / 2; i += pts::NTH) rowstart[i] = a.rowstart[i + N / 2];
 
-    // the tile's centre (relative to the grid's centre) in FP32: the plane tests carry margins of
-    // 2e-3 and more against its rounding (< 3e-5 at |c| <= 512), and the candidate rows one row.
-    // These tile constants are the same in every lane; they are kept in LDS (geo) and read where
-    // they are used, since vector registers holding them across the loops below would spill.
-    enum { G_TC0, G_TC1, G_TC2, G_BLO0, G_BLO1, G_BLO2, G_BHI0, G_BHI1, G_BHI2, G_RK, G_INVS, G_N };
-    // candidate rows of a view: the k1 within rk of the projection u1 of the tile's centre onto the
-    // plane (rk: the circumscribed sphere's radius in lattice units), widened by 1e-3 for the
-    // rounding of u1: S = floor(2 rk + 2e-3) + 2 rows from ceil(u1 - rk - 1e-3)
-    const int S = (int)floorf(2.f * ((T * 0.8660254f + 1e-3f) / (float)a.s) + 2e-3f) + 2;
-    if (tid == 0) {
-        // positions tau whose (clamped) cell lies in the tile, widened by a margin far above the
-        // rounding of the FP32 row intervals; the edge tiles also own the clamped cells beyond the
-        // grid.  Each interval is then trimmed to the exact one with the FP64 cell test.
-        constexpr float MARGIN = 1e-2f, FAR = 1e30f;
-        const int tt[3] = {tt0, tt1, tt2};
-        for (int d = 0; d < 3; ++d) {
-            geo[G_TC0 + d] = tt[d] * T + 0.5f * T - 0.5f * L;
-            geo[G_BLO0 + d] = tt[d] == 0 ? -FAR : tt[d] * T - MARGIN;
-            geo[G_BHI0 + d] = (tt[d] + 1) * T >= L ? FAR : (tt[d] + 1) * T + MARGIN;
-        }
-        geo[G_RK] = (T * 0.8660254f + 1e-3f) / (float)a.s;
-        geo[G_INVS] = 1.f / (float)a.s;
-    }
-    if (tid < 64) {
-        // footprint cell (j2, j3) of each lane: lane group g holds the rows assigned to it, W lanes
-        // per row; kept in LDS and read where the adds need it (registers holding it across the
-        // staging would spill)
-        const int lane = tid;
-        int j2 = 0, j3 = 0;
-        bool act = false;
-        if constexpr (GROUPS >= 0) {
-            const int g = lane / (64 / G), idx = lane % (64 / G), rank = idx / W;
-            int seen = 0;
-#pragma unroll
-            for (int r = 0; r < W; ++r) {
-                if (((GROUPS >> (2 * r)) & 3) != g) continue;
-                if (seen == rank) {
-                    j2 = r;
-                    j3 = idx - rank * W;
-                    act = true;
-                }
-                ++seen;
-            }
-        } else {
-            act = lane < W * W;
-            const int jl = act ? lane : 0;
-            j2 = jl / W;
-            j3 = jl - j2 * W;
-        }
-        lmap[lane] = (unsigned short)(j2 | (j3 << 4) | ((int)act << 8));
-    }
-    __syncthreads();  // the counters, the tile constants, the lane map and the row starts are in place
-    const int N2 = N * N;
-
-    // points of the queue [0, nq) staged and accumulated in batches of SP_PB
-    auto process = [&](int nq) {
-        if (tid == 0 && nq > 0) any = 1;
-        // tile coordinates as values: a select between the captured references would be a
-        // select between addresses, which puts them in scratch memory
-        const int tv0 = tt0, tv1 = tt1, tv2 = tt2;
-        const int wv = tid >> 6, lane = tid & 63;
-        for (int pb = 0; pb < nq; pb += SP_PB) {
-            const int nb = min(SP_PB, nq - pb);
-            // stage the batch: one item per (point, axis), spread over all threads, computes the
-            // window start and weights along that axis; the axis-0 item also computes the point's
-            // value and folds it, in fixed-point units, into its weights.  The point keeps its
-            // batch position.
-            float ph[NIT][W];
-            int lod[NIT], pp[NIT], dd[NIT];
-            float scale = 1.f;
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                const int i = tid + it * SP_THREADS;
-                dd[it] = -1;
-                pp[it] = 0;
-                lod[it] = 0;
-                if (i < 3 * nb) {
-                    const int d = i / nb, p = i - d * nb;
-                    dd[it] = d;
-                    pp[it] = p;
-                    const int e = queue[pb + p];
-                    const int sl = e >> 18, k1 = ((e >> 9) & 511) - 256, k2 = (e & 511) - 256;
-                    const int m = img_m[sl];
-                    const double* c = a.c12 + 6 * (int64_t)m;
-                    const int ttd = d == 0 ? tv0 : (d == 1 ? tv1 : tv2);
-                    // |t_d| <= L/2 in exact arithmetic; clamp the rounding excess so the
-                    // stencil stays inside the padded tile for every width
-                    const double tau = fmin(fmax(tau_of(a.s, k1, k2, c[d], c[3 + d], halfL), 0.0), (double)L);
-                    const double left = tau - 0.5 * W;
-                    const int b0 = (int)floor(left) + 1;
-                    const float f = (float)((double)b0 - left);  // in (0, 1]
-                    kb_weights<W>(a.poly, 2.f * f - 1.f, ph[it]);
-                    // in [0, PT - W] for every point of the tile (clamped position); the bound
-                    // also keeps the LDS accesses inside the tile should rounding ever differ
-                    lod[it] = min(max(b0 - (ttd * T - PADLO), 0), PT - W);
-                    if (d == 0) {
-                        const int g = CPLX ? img_g[sl] : a.group[m];
-                        const float h = a.table ? a.table[(int64_t)g * a.Q + k1 * k1 + k2 * k2] : 1.f;
-                        if constexpr (!CPLX) {
-                            scale = 2.f * h * h * fxs;
-                        } else {
-                            // h exp(i theta) (b(k) + conj b(-k)), theta = 2 pi <k, s_m> / N (re-centring)
-                            const int idx = rs_l[k1 + N / 2] + k2;
-                            const int64_t mo = img_o[sl];  // the caller's view index
-                            const float2 bp = a.b[mo * a.P + idx];
-                            const float2 bm = a.b[mo * a.P + (a.P - 1 - idx)];
-                            const float sr = bp.x + bm.x, si = bp.y - bm.y;
-                            float cs = 1.f, sn = 0.f;
-                            if (a.shifts) {
-                                // theta / 2 pi reduced to [-1/2, 1/2] in FP64, then the FP32 sine and
-                                // cosine of pi times twice that
-                                const double f = (k1 * a.shifts[2 * (int64_t)m] + k2 * a.shifts[2 * (int64_t)m + 1]) / N;
-                                sincospif((float)(2.0 * (f - rint(f))), &sn, &cs);
-                            }
-                            scale = fxs * h * (a.comp ? cs * si + sn * sr : cs * sr - sn * si);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                const int d = dd[it];
-                if (d < 0) continue;
-                // weights of axis d at W d, window starts in the bytes of pt_lo
-                float* q = pt_w + pp[it] * PSTR + W * d;
-#pragma unroll
-                for (int j = 0; j < W; ++j) q[j] = d == 0 ? scale * ph[it][j] : ph[it][j];
-                reinterpret_cast<unsigned char*>(pt_lo)[4 * pp[it] + d] = (unsigned char)lod[it];
-            }
-            __syncthreads();
-            // The wavefronts take the batch's points in turn, the lanes on the W x W footprint of
-            // axes 1 and 2, one 64-bit integer atomic add per cell and window row.  Integer
-            // addition is associative, so the tile is exact and independent of the order of the
-            // adds; each term is the FP32 product rounded to an integer (|term| < 2^31 by the
-            // choice of fxs).  A wavefront takes FQ of its points at a time: their window words and
-            // axis-0 weights (the same for every lane) arrive in one LDS read spread over the
-            // lanes and are then broadcast from registers (readlane); each footprint lane reads
-            // its own axis-1 and axis-2 weights.  All reads of the FQ points come before their
-            // adds, so the wavefront waits once per FQ points (LDS completes in order, so a read
-            // issued after adds waits for them).  The lanes off the footprint take part in the
-            // reads only.
-            const int lm = lmap[lane];
-            const int j2 = lm & 15, j3 = (lm >> 4) & 15;
-            const bool act = (lm >> 8) != 0;
-            static_assert(FQ == 4, "the register list of the asm statement below names 4");
-            static_assert(FQ * 8 + FQ <= 64, "one read for the uniform data");
-            const int wvu = __builtin_amdgcn_readfirstlane(wv);
-            // lane roles of the uniform read: 8 q + k -> weight k of point q (k < 8); 32 + q -> window
-            // word of point q; the other lanes repeat point q's window word
-            const int uq = lane < 32 ? (lane >> 3) : (lane - 32) % FQ;
-            // the adds at a raised wavefront priority: where the two workgroups of a CU are in
-            // different phases, the issue of the LDS-bound adds goes first and the staging or
-            // enumeration of the other, bound by load latency, fills the gaps
-            __builtin_amdgcn_s_setprio(2);
-            for (int p0 = wvu; p0 < nb; p0 += FQ * SP_WAVES) {
-                int pq[FQ];
-#pragma unroll
-                for (int q = 0; q < FQ; ++q) pq[q] = min(p0 + q * SP_WAVES, nb - 1);
-                int pl = pq[0];
-#pragma unroll
-                for (int q = 1; q < FQ; ++q) pl = uq == q ? pq[q] : pl;
-                const float* src = lane < 32 ? pt_w + pl * PSTR + (lane & 7) : reinterpret_cast<const float*>(pt_lo + pl);
-                float w2[FQ], w3[FQ];
-#pragma unroll
-                for (int q = 0; q < FQ; ++q) {
-                    w2[q] = pt_w[pq[q] * PSTR + W + j2];
-                    w3[q] = pt_w[pq[q] * PSTR + 2 * W + j3];
-                }
-                float u = *src;
-                // all the reads are issued here, before any register of theirs is used
-                asm volatile("" : "+v"(u), "+v"(w2[0]), "+v"(w3[0]), "+v"(w2[1]), "+v"(w3[1]),
-                             "+v"(w2[2]), "+v"(w3[2]), "+v"(w2[3]), "+v"(w3[3]));
-                if (!act) continue;
-#pragma unroll
-                for (int q = 0; q < FQ; ++q) {
-                    if (p0 + q * SP_WAVES >= nb) break;
-                    const float w23 = w2[q] * w3[q];
-                    const int lw = __builtin_amdgcn_readlane(__float_as_int(u), 32 + q);
-                    const int cb = (lw & 255) * PP + (((lw >> 8) & 255) + j2) * RP + ((lw >> 16) & 255) + j3;
-#pragma unroll
-                    for (int r = 0; r < W; ++r) {
-                        const float wxr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(u), 8 * q + r));
-                        // Ker: non-negative terms; a component of complex data: signed terms
-                        const unsigned long long t = CPLX ? (unsigned long long)(long long)(int)rintf(wxr * w23)
-                                                          : (unsigned long long)(unsigned)fmaf(wxr, w23, 0.5f);
-                        __hip_atomic_fetch_add(&tile64[cb + r * PP], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                }
-            }
-            __builtin_amdgcn_s_setprio(0);
-            __syncthreads();
-        }
+    auto begin = [&]() {
+        for (int i = tid; i < NC * T::CELLS; i += pts::NTH) (&tile[0][0])[i] = 0ull;
     };
-
-
-    // the point (k1, k2) of the view with columns c lies in the tile (the test that decides
-    // which tile spreads a point): inside the disk and its clamped cell in the tile per axis
-    auto in_tile = [&](const double* c, int k1, int k2) {
-        if (4 * (k1 * k1 + k2 * k2) > N2) return false;
-        bool in = true;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            int cell = (int)floor(tau_of(a.s, k1, k2, c[d], c[3 + d], halfL));
-            cell = cell < 0 ? 0 : (cell > L - 1 ? L - 1 : cell);
-            in = in && (cell / T == (d == 0 ? tt0 : (d == 1 ? tt1 : tt2)));
-        }
-        return in;
+    struct Raw {
+        float h;
+        float2 bp, bm;
+        double s1, s2;
     };
-
-    // the view slots and the queue persist across the image chunks, so that batches are full:
-    // queued points name their view by slot, and the slots are reused only after the queue has
-    // been processed.  A chunk is VPT views per thread (the fixed cost of a chunk, barriers and
-    // the latency of the view data, is paid once for all of them).
-    constexpr int VPT = 8;
-    __shared__ unsigned bmask[SP_THREADS / 32];  // the live blocks of the current group of blocks
-    // a chunk's live blocks (in the group), their count, and the next block of the group to look at
-    __shared__ int lblk[VPT + 2];
-    int base = 0;  // first slot whose rows are not yet enumerated
-    // blocks of SP_THREADS views (the work range starts on a block)
-    const int blk0 = wk.y / SP_THREADS, blk1 = (wk.z + SP_THREADS - 1) / SP_THREADS;
-    for (int gb = blk0; gb < blk1; gb += SP_THREADS) {
-        // block tests, one block per thread, up to SP_THREADS blocks at a time: a block whose box
-        // of normals n gives no |n . c| within the bound below for the tile's centre c holds no
-        // view that meets the tile.  The chunks below visit the live blocks only.
-        if (tid < SP_THREADS / 32) bmask[tid] = 0u;
-        __syncthreads();
-        if (gb + tid < blk1) {
-            const float tc0 = geo[G_TC0], tc1 = geo[G_TC1], tc2 = geo[G_TC2];
-            const float4 lo = a.vbox[2 * (gb + tid)], hi = a.vbox[2 * (gb + tid) + 1];
-            const float p0 = tc0 * lo.x, q0 = tc0 * hi.x, p1 = tc1 * lo.y, q1 = tc1 * hi.y;
-            const float p2 = tc2 * lo.z, q2 = tc2 * hi.z;
-            const float dmin = fminf(p0, q0) + fminf(p1, q1) + fminf(p2, q2);
-            const float dmax = fmaxf(p0, q0) + fmaxf(p1, q1) + fmaxf(p2, q2);
-            const float lim = 0.5f * T * lo.w + 3e-3f;
-            if (dmin <= lim && dmax >= -lim) atomicOr(&bmask[tid >> 5], 1u << (tid & 31));
-        }
-        if (tid == 0) lblk[VPT + 1] = 0;
-        while (true) {
-            __syncthreads();  // the mask is complete, and the last chunk's blocks are no longer read
-            if (tid == 0) {
-                int n = 0, cur = lblk[VPT + 1];
-                while (n < VPT && cur < SP_THREADS) {
-                    const unsigned w = bmask[cur >> 5] & (~0u << (cur & 31));
-                    if (w == 0u) {
-                        cur = (cur | 31) + 1;
-                        continue;
-                    }
-                    const int b = (cur & ~31) + __builtin_ctz(w);
-                    lblk[n++] = b;
-                    cur = b + 1;
-                }
-                lblk[VPT] = n;
-                lblk[VPT + 1] = cur;
-            }
-            __syncthreads();
-            const int nl = lblk[VPT];
-            if (nl == 0) break;
-            // a chunk: the views of up to VPT live blocks, one per thread and block
-            unsigned pendv = 0u;  // this thread's views of the chunk that meet the tile, not yet in a slot
-            {
-                float4 nv[VPT];
-                unsigned livev = 0u;
-#pragma unroll
-                for (int v = 0; v < VPT; ++v) {
-                    const int m = v < nl ? (gb + lblk[v]) * SP_THREADS + tid : wk.z;
-                    const bool live = m < wk.z;
-                    nv[v] = live ? *reinterpret_cast<const float4*>(a.nrm + 4 * (int64_t)m) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    livev |= (unsigned)live << v;
-                }
-    #pragma unroll
-                for (int v = 0; v < VPT; ++v) {
-                    // the plane meets the tile's cube: distance of the centre at most the cube's half
-                    // extent along the normal
-                    if (((livev >> v) & 1u) && fabsf(geo[G_TC0] * nv[v].x + geo[G_TC1] * nv[v].y + geo[G_TC2] * nv[v].z) <=
-                                                    0.5f * T * (fabsf(nv[v].x) + fabsf(nv[v].y) + fabsf(nv[v].z)) + 2e-3f)
-                        pendv |= 1u << v;
-                }
-            }
-            while (true) {
-                // slots for the surviving views while free ones last
-                for (int v = 0; v < VPT; ++v) {
-                    if (!((pendv >> v) & 1u)) continue;
-                    const int sl = atomicAdd(&nimg, 1);
-                    if (sl < SP_THREADS) {
-                        img_m[sl] = (gb + lblk[v]) * SP_THREADS + tid;
-                        pendv &= ~(1u << v);
-                    }
-                }
-                __syncthreads();
-                const int top = min(nimg, SP_THREADS);
-                if constexpr (CPLX) {
-                    // the new slots' CTF groups and views in the caller's order, read once per slot
-                    // here (in parallel) rather than by the staging of every point
-                    if (tid >= base && tid < top) {
-                        const int m = img_m[tid];
-                        img_o[tid] = a.vorder[m];
-                        img_g[tid] = a.group[m];
-                    }
-                    __syncthreads();
-                }
-                // one (view, row k1) per thread: the k2 interval whose cells lie in the tile (three slabs,
-                // plus the disk and half-disk bounds), trimmed to the exact test at both ends (the cell
-                // along a row is monotone in k2, so the points that pass form an interval), then the
-                // points are queued.  A reservation that does not fit waits for the queue's whole
-                // batches to be processed; the reservations that fitted form the prefix up to the
-                // first that did not.
-                const int units = (top - base) * S;
-                for (int ub = 0; ub < units; ub += SP_THREADS) {
-                    const int u = ub + tid;
-                    int sl = 0, k1 = 0, klo = 0, cnt = 0;
-                    if (u < units) {
-                        const int v = u / S;
-                        sl = base + v;
-                        const double* c = a.c12 + 6 * (int64_t)img_m[sl];
-                        const float u1 = (geo[G_TC0] * (float)c[0] + geo[G_TC1] * (float)c[1] + geo[G_TC2] * (float)c[2]) *
-                                         geo[G_INVS];
-                        k1 = (int)ceilf(u1 - geo[G_RK] - 1e-3f) + (u - v * S);
-                        if (k1 >= 0 && 4 * k1 * k1 <= N2) {
-                            const int kd = (int)sqrtf((float)(N2 / 4 - k1 * k1)) + 1;  // >= the disk's |k2|
-                            float lo = (float)-kd, hi = (float)kd;
-                            bool ok = true;
-    #pragma unroll
-                            for (int d = 0; d < 3; ++d) {
-                                const float bl = geo[G_BLO0 + d], bh = geo[G_BHI0 + d];
-                                const float al = (float)(a.s * k1 * c[d] + halfL), be = (float)(a.s * c[3 + d]);
-                                if (fabsf(be) < 1e-6f) {
-                                    ok = ok && al >= bl && al <= bh;
-                                } else {
-                                    // reciprocal to about 1 ulp: far inside the bounds' margin
-                                    const float rb = __builtin_amdgcn_rcpf(be);
-                                    const float t1 = (bl - al) * rb, t2 = (bh - al) * rb;
-                                    lo = fmaxf(lo, fminf(t1, t2));
-                                    hi = fminf(hi, fmaxf(t1, t2));
-                                }
-                            }
-                            klo = (int)ceilf(lo);
-                            if (k1 == 0) klo = max(klo, 1);
-                            int khi = (int)floorf(hi);
-                            if (ok) {
-                                while (klo <= khi && !in_tile(c, k1, klo)) ++klo;
-                                while (khi >= klo && !in_tile(c, k1, khi)) --khi;
-                                // a row crosses a tile in at most T sqrt(3) / s + 1 points
-                                cnt = min(khi - klo + 1, 32);
-                            }
-                        }
-                    }
-                    bool pend = cnt > 0;
-                    while (true) {
-                        if (pend) {
-                            const int pos = atomicAdd(&qn, cnt);
-                            if (pos + cnt <= QCAP) {
-                                for (int j = 0; j < cnt; ++j) queue[pos + j] = (sl << 18) | ((k1 + 256) << 9) | (klo + j + 256);
-                                pend = false;
-                            } else {
-                                atomicMin(&qfail, pos);
-                            }
-                        }
-                        if (!__syncthreads_or(pend)) break;
-                        // the queue is full: process its whole batches and keep the rest at its front
-                        const int nv = min(qfail, qn);
-                        const int nfull = nv / SP_PB * SP_PB;
-                        process(nfull);
-                        const int rest = nv - nfull;
-                        const int keep = tid < rest ? queue[nfull + tid] : 0;
-                        __syncthreads();
-                        if (tid < rest) queue[tid] = keep;
-                        if (tid == 0) { qn = rest; qfail = QCAP; }
-                        __syncthreads();
-                    }
-                }
-                base = top;
-                if (!__syncthreads_or(pendv != 0u)) break;
-                // the slots ran out: process everything queued, then reuse them
-                process(qn);
-                __syncthreads();
-                if (tid == 0) { qn = 0; qfail = QCAP; nimg = 0; }
-                __syncthreads();
-                base = 0;
+    auto fetch = [&](int m, int k1, int k2) {
+        Raw x{};
+        const float4 rec = a.p.vrec[2 * (int64_t)m + 1];
+        const int g = __float_as_int(rec.z);
+        if constexpr (CPLX) {
+            const int64_t mo = (int64_t)__float_as_int(rec.w) * a.P;  // the caller's view
+            const int idx = rowstart[k1] + k2;
+            x.bp = a.b[mo + idx];
+            x.bm = a.b[mo + (a.P - 1 - idx)];
+            if (a.shifts) {
+                x.s1 = a.shifts[2 * (int64_t)m];
+                x.s2 = a.shifts[2 * (int64_t)m + 1];
             }
         }
-    }
-    __syncthreads();
-    process(qn);
-    __syncthreads();
-    if (!any) return;
-    const int o0 = tt0 * T - PADLO, o1 = tt1 * T - PADLO, o2 = tt2 * T - PADLO;
-    for (int i = tid; i < NCELL; i += SP_THREADS) {
-        const int l0 = i / (PT * PT), l1 = (i / PT) % PT, l2 = i % PT;
-        const int li = l0 * PP + l1 * RP + l2;
-        // grid index = position mod L, position = cell - L/2
-        const int g0 = ((o0 + l0 - L / 2) % L + L) % L;
-        const int g1 = ((o1 + l1 - L / 2) % L + L) % L;
-        const int g2 = ((o2 + l2 - L / 2) % L + L) % L;
-        const int64_t gi = ((int64_t)g0 * L + g1) * L + g2;
-        // the exact integer sum, rounded once to FP32; complex data: component a.comp
+        x.h = a.table ? a.table[(int64_t)g * a.Q + k1 * k1 + k2 * k2] : 1.f;
+        return x;
+    };
+    auto value = [&](const Raw& x, int k1, int k2, float* v) {
         if constexpr (!CPLX) {
-            const unsigned long long v = tile64[li];
-            if (v) unsafeAtomicAdd(reinterpret_cast<float*>(a.grid) + gi, (float)((double)v * fx_inv));
+            v[0] = bounded(2.f * x.h * x.h * fxs);
         } else {
-            const long long v = (long long)tile64[li];
-            if (v) unsafeAtomicAdd(reinterpret_cast<float*>(a.grid) + 2 * gi + a.comp, (float)((double)v * fx_inv));
+            // h exp(i theta) (b(k) + conj b(-k)), theta = 2 pi <k, s_m> / N (re-centring)
+            const float sr = x.bp.x + x.bm.x, si = x.bp.y - x.bm.y;
+            float cs = 1.f, sn = 0.f;
+            if (a.shifts) {
+                // theta / 2 pi reduced to [-1/2, 1/2] in FP64, then the FP32 sine and cosine of pi
+                // times twice that (N is a power of 2: the product with 1 / N is the quotient)
+                const double f = (k1 * x.s1 + k2 * x.s2) * inv_n;
+                sincospif((float)(2.0 * (f - rint(f))), &sn, &cs);
+            }
+            v[0] = bounded(fxs * x.h * (cs * sr - sn * si));
+            v[1] = bounded(fxs * x.h * (cs * si + sn * sr));
         }
-    }
+    };
+    // A lane's part of the 16 x CJ x 8 footprint: columns (axis 1, axis 2) = (NJ e + n, kk), rows
+    // (axis 0) 4 q + r of accumulator register r; as an operand, point q of the four, row lane & 15.
+    const int q = lane >> 4, e = (lane >> 3) & 1, kk = lane & 7;
+    pts::f4 acc[NC][NJ];
+    auto open = [&](int) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int n = 0; n < NJ; ++n) acc[c][n] = pts::f4{0.f, 0.f, 0.f, 0.f};
+    };
+    const float* const wave = s.wave[tid >> 6];
+    const float* const row0 = wave + T::LEAD + q * T::S0 + (lane & 15);
+    const float* const rowb = wave + T::LEAD + 16 * T::S0 + q * T::SB;
+    auto round = [&](int cnt, int) {
+        // the operands of KB steps (four points each) are read together, then used
+        constexpr int KB = NJ == 4 ? 4 : 1;
+#pragma unroll
+        for (int kb = 0; kb < 4; kb += KB) {
+            float w0[KB], v0[KB], v1[KB], w2[KB], w1[KB][NJ];
+#pragma unroll
+            for (int j = 0; j < KB; ++j) {
+                const float* r = rowb + 4 * (kb + j) * T::SB;
+                v0[j] = r[T::OFFV];
+                v1[j] = CPLX ? r[T::OFFV + 2] : 0.f;
+                const int o = __float_as_int(r[T::OFFV + 1]);
+                w0[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row0 + 4 * (kb + j) * T::S0) + o);
+                w2[j] = r[T::CJ + kk];
+#pragma unroll
+                for (int n = 0; n < NJ; n += 4) {
+                    const pts::f4 v = *reinterpret_cast<const pts::f4*>(r + NJ * e + n);
+                    w1[j][n] = v.x; w1[j][n + 1] = v.y; w1[j][n + 2] = v.z; w1[j][n + 3] = v.w;
+                }
+            }
+            if constexpr (KB == 4) {  // all of the reads are issued before the first product waits for one
+                asm volatile("" : "+v"(w0[0]), "+v"(w0[1]), "+v"(w0[2]), "+v"(w0[3]), "+v"(w2[0]), "+v"(w2[1]),
+                             "+v"(w2[2]), "+v"(w2[3]));
+            }
+#pragma unroll
+            for (int j = 0; j < KB; ++j) {
+                if (4 * (kb + j) >= cnt) break;
+                const float a0[2] = {w0[j] * v0[j], w0[j] * v1[j]};
+#pragma unroll
+                for (int n = 0; n < NJ; ++n) {
+                    const float w12 = w1[j][n] * w2[j];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        acc[c][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[c], w12, acc[c][n], 0, 0, 0);
+                }
+            }
+        }
+    };
+    auto close = [&](int bin) {
+        const int o0 = bin / (T::NB1 * T::NB2) * T::B0, o1 = bin / T::NB2 % T::NB1 * T::B1, o2 = bin % T::NB2 * T::B2;
+        const int cell = ((o0 + 4 * q) * T::P1 + o1 + NJ * e) * T::RP + o2 + kk;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int n = 0; n < NJ; ++n)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    __hip_atomic_fetch_add(&tile[c][cell + (r * T::P1 + n) * T::RP], to_units(acc[c][n][r]),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    const int L = a.p.L;
+    pts::for_items<T>(a.p, s, [&](int4 wk) {
+        const int nt12 = a.p.nt1 * a.p.nt2;
+        const int t0 = wk.x / nt12 * T::T0, t1 = wk.x / a.p.nt2 % a.p.nt1 * T::T1, t2 = wk.x % a.p.nt2 * T::T2;
+        pts::for_points<T>(a.p, s, wk, t0, t1, t2, begin, fetch, value, open, round, close);
+        if (!s.any) return;
+        for (int i = tid; i < T::P0 * T::P1 * T::P2; i += pts::NTH) {
+            const int l0 = i / (T::P1 * T::P2), l1 = i / T::P2 % T::P1, l2 = i % T::P2;
+            const int li = (l0 * T::P1 + l1) * T::RP + l2;
+            // grid index = position mod L, position = cell - L/2
+            const int g0 = ((t0 - T::PADLO + l0 - L / 2) % L + L) % L;
+            const int g1 = ((t1 - T::PADLO + l1 - L / 2) % L + L) % L;
+            const int g2 = ((t2 - T::PADLO + l2 - L / 2) % L + L) % L;
+            const int64_t gi = ((int64_t)g0 * L + g1) * L + g2;
+            // the integer sum, rounded once to FP32
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const long long v = (long long)tile[c][li];
+                if (v) unsafeAtomicAdd(reinterpret_cast<float*>(a.grid) + NC * gi + c, (float)((double)v * fx_inv));
+            }
+        }
+    });
 }
 
 // bits of the largest |component| of n complex values (atomic max on the bits of non-negative
@@ -684,70 +299,81 @@ __global__ void k_f2d(const float* __restrict__ a, double* __restrict__ o, int64
 
 int grid_blocks(int64_t n) { return (int)std::min<int64_t>((n + 255) / 256, 65536); }
 
-// 8 wavefronts per workgroup; the tile and the staging fit two workgroups in the LDS of a compute
-// unit (one for W = 8).
-template <int T, bool CPLX, int NTH = 512>
+template <int W, bool CPLX>
+hipError_t launch_w(firm_plan p, SpreadArgs& a, int nwork) {
+    using T = SpreadTile<W, CPLX>;
+    a.p.nt1 = (a.p.L + T::T1) / T::T1;  // starts 0 .. L
+    a.p.nt2 = (a.p.L + T::T2) / T::T2;
+    hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, p->stream, reinterpret_cast<unsigned*>(a.p.taken), 0u);
+    hipLaunchKernelGGL((k_spread<W, CPLX>), dim3(std::min(nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
+    return hipGetLastError();
+}
+
+template <bool CPLX>
 hipError_t launch_spread(firm_plan p, int L, const int* work, int nwork, void* grid, const float2* b, float fxs,
-                         const unsigned* fx_bmax = nullptr, float fx_coef = 0.f, int comp = 0) {
+                         const unsigned* fx_bmax = nullptr, float fx_coef = 0.f) {
     SpreadArgs a;
-    a.N = p->N; a.M = p->M; a.L = L; a.nt = (L + T - 1) / T;
-    a.s = (double)L / p->N;
-    a.c12 = p->c12s; a.nrm = p->nrms; a.group = p->groups; a.table = p->table; a.Q = p->Q;
-    a.poly = p->kb_poly; a.work = reinterpret_cast<const int4*>(work); a.grid = grid;
+    a.p = point_args(p, L, work, nwork);
+    a.table = p->table; a.Q = p->Q; a.grid = grid;
     a.b = b; a.shifts = p->shiftss; a.rowstart = p->rowstart; a.P = p->P;
-    a.vorder = p->vorder; a.vbox = p->vbox;
-    static_assert(NTH == SP_VBLK, "a culling round's view blocks are the host's normal-box blocks");
     a.fxs = fxs; a.fx_inv = 1.0 / (double)fxs;
-    a.fx_bmax = fx_bmax; a.fx_coef = fx_coef; a.comp = comp;
+    a.fx_bmax = fx_bmax; a.fx_coef = fx_coef;
     if (nwork == 0) return hipSuccess;
     switch (p->kbw) {
-        case 4: hipLaunchKernelGGL((k_spread<T, 4, CPLX, NTH>), dim3(nwork), dim3(NTH), 0, p->stream, a); break;
-        case 5: hipLaunchKernelGGL((k_spread<T, 5, CPLX, NTH>), dim3(nwork), dim3(NTH), 0, p->stream, a); break;
-        case 6: hipLaunchKernelGGL((k_spread<T, 6, CPLX, NTH>), dim3(nwork), dim3(NTH), 0, p->stream, a); break;
-        case 7: hipLaunchKernelGGL((k_spread<T, 7, CPLX, NTH>), dim3(nwork), dim3(NTH), 0, p->stream, a); break;
-        case 8: hipLaunchKernelGGL((k_spread<T, 8, CPLX, NTH>), dim3(nwork), dim3(NTH), 0, p->stream, a); break;
+        case 4: return launch_w<4, CPLX>(p, a, nwork);
+        case 5: return launch_w<5, CPLX>(p, a, nwork);
+        case 6: return launch_w<6, CPLX>(p, a, nwork);
+        case 7: return launch_w<7, CPLX>(p, a, nwork);
+        case 8: return launch_w<8, CPLX>(p, a, nwork);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+}
+
+template <bool CPLX>
+TileDims spread_dims(int W) {
+    switch (W) {
+        case 4: return tile_dims<SpreadTile<4, CPLX>>();
+        case 5: return tile_dims<SpreadTile<5, CPLX>>();
+        case 6: return tile_dims<SpreadTile<6, CPLX>>();
+        case 7: return tile_dims<SpreadTile<7, CPLX>>();
+        default: return tile_dims<SpreadTile<8, CPLX>>();
+    }
 }
 
 }  // namespace
 
-#define SP_TILE_REAL 13
-#define SP_TILE_CPLX 12
-
-// Host work list: tiles of an L^3 grid that can hold points (|centre| - R <= L/2), each
-// split into image ranges, ordered by expected work (tiles near the origin meet every image plane)
-// so that the heavy ones start first.  The ranges hold about 1 / SP_ITEMS of all expected
-// (tile, image) meetings: the tiles at the origin meet every image, and one workgroup for up to
-// 16,384 images left them running alone (A*b at N = 64 with 9,973 images: 21.9 -> 9.1 ms; the
-// kernel at N = 16 with about 10^4 images 3.8 -> 2.0 ms; N = 256 with 10^5 images unchanged).
+// Host work list: tiles of T0 x T1 x T2 cells of an L^3 grid that can hold points, each split
+// into view ranges, ordered by expected work (tiles near the origin meet every view's plane) so
+// that the heavy ones start first.  The ranges hold about 1 / SP_ITEMS of all expected (tile, view)
+// meetings: the tiles at the origin meet every view, and one workgroup for up to 16,384 views left
+// them running alone (A*b at N = 64 with 9,973 views: 21.9 -> 9.1 ms).  `last`: the last
+// cell that a tile may own (L - 1, or L for window starts); `shift`: the position of cell 0's lower
+// edge; ranges start on multiples of `gran` views.
 #define SP_ITEMS 2048
-std::vector<int> spread_worklist(int L, int T, int M, double s) {
-    const int nt = (L + T - 1) / T;
-    const double Rt = T * 0.8660254037844386;
+std::vector<int> spread_worklist(int L, TileDims T, int last, double shift, int M, int gran) {
+    const int T0 = T.t0, T1 = T.t1, T2 = T.t2;
+    const int n0 = last / T0 + 1, n1 = last / T1 + 1, n2 = last / T2 + 1;
+    const double Rt = 0.5 * std::sqrt((double)T0 * T0 + (double)T1 * T1 + (double)T2 * T2);
     struct Tile { double expect; int t; };
     std::vector<Tile> tiles;
     double total = 0.0;
-    for (int a = 0; a < nt; ++a)
-        for (int b = 0; b < nt; ++b)
-            for (int c = 0; c < nt; ++c) {
-                const double x = a * T + 0.5 * T - 0.5 * L, y = b * T + 0.5 * T - 0.5 * L,
-                             z = c * T + 0.5 * T - 0.5 * L;
+    for (int a = 0; a < n0; ++a)
+        for (int b = 0; b < n1; ++b)
+            for (int c = 0; c < n2; ++c) {
+                const double o = shift - 0.5 * L;
+                const double x = (a + 0.5) * T0 + o, y = (b + 0.5) * T1 + o, z = (c + 0.5) * T2 + o;
                 const double rho = std::sqrt(x * x + y * y + z * z);
                 if (rho - Rt > 0.5 * L + 1.0) continue;
                 const double expect = (rho <= Rt ? 1.0 : Rt / rho) * M;
-                tiles.push_back({expect, (a * nt + b) * nt + c});
+                tiles.push_back({expect, (a * n1 + b) * n2 + c});
                 total += expect;
             }
-    const double chunk = std::min(16384.0, std::max((double)SP_VBLK, total / SP_ITEMS));
+    const double chunk = std::max((double)gran, total / SP_ITEMS);
     struct Item { double w; int t, m0, m1; };
     std::vector<Item> items;
     for (const Tile& t : tiles) {
         const int nch = std::max(1, (int)std::ceil(t.expect / chunk));
-        // ranges start on multiples of SP_VBLK: the spread's culling rounds read the normal
-        // boxes of whole blocks
-        const int per = ((M + nch - 1) / nch + SP_VBLK - 1) / SP_VBLK * SP_VBLK;
+        const int per = ((M + nch - 1) / nch + gran - 1) / gran * gran;
         for (int k = 0; k < nch; ++k) {
             const int m0 = k * per, m1 = std::min(M, m0 + per);
             if (m0 < m1) items.push_back({t.expect / nch, t.t, m0, m1});
@@ -757,12 +383,15 @@ std::vector<int> spread_worklist(int L, int T, int M, double s) {
     std::vector<int> out;
     out.reserve(items.size() * 4);
     for (auto& it : items) { out.push_back(it.t); out.push_back(it.m0); out.push_back(it.m1); out.push_back(0); }
-    (void)s;
     return out;
 }
 
-int spread_tile_real() { return SP_TILE_REAL; }
-int spread_tile_cplx() { return SP_TILE_CPLX; }
+// The work lists of the kernel's spread (cplx = false, grid 4N) and A*b's (grid 2N): tiles of window
+// starts 0 .. L, whose first one lies half a cell below zero for odd widths.
+std::vector<int> spread_points_worklist(int N, int W, int M, bool cplx) {
+    const int L = (cplx ? 2 : 4) * N;
+    return spread_worklist(L, cplx ? spread_dims<true>(W) : spread_dims<false>(W), L, W % 2 ? -0.5 : 0.0, M, 4 * SP_VRUN);
+}
 
 hipError_t fill_zero(void* ptr, size_t bytes, hipStream_t s) {
     const size_t n4 = bytes / 16;
@@ -776,7 +405,7 @@ hipError_t fill_zero(void* ptr, size_t bytes, hipStream_t s) {
 }
 
 hipError_t spread_ker(firm_plan p, float* grid) {
-    return launch_spread<SP_TILE_REAL, false>(p, 4 * p->N, p->tiles_ker, p->ntiles_ker, grid, nullptr, p->fx_ker);
+    return launch_spread<false>(p, 4 * p->N, p->tiles_ker, p->ntiles_ker, grid, nullptr, p->fx_ker);
 }
 
 hipError_t spread_atb(firm_plan p, const float2* b, float2* grid) {
@@ -787,13 +416,7 @@ hipError_t spread_atb(firm_plan p, const float2* b, float2* grid) {
                        reinterpret_cast<const float4*>(b), n / 2, b + (n / 2) * 2, (int)(n % 2), p->fx_bmax);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // one component per launch: a one-plane tile leaves room for two workgroups per CU
-    for (int comp = 0; comp < 2; ++comp) {
-        e = launch_spread<SP_TILE_CPLX, true>(p, 2 * p->N, p->tiles_atb, p->ntiles_atb, grid, b, 1.f,
-                                                         p->fx_bmax, p->fx_atb_coef, comp);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return launch_spread<true>(p, 2 * p->N, p->tiles_atb, p->ntiles_atb, grid, b, 1.f, p->fx_bmax, p->fx_atb_coef);
 }
 
 hipError_t atb_k0_term(firm_plan p, const float2* b, double* out) {
