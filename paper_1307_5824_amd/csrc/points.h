@@ -14,7 +14,8 @@
 // cells of the point's window; one 64-bit LDS atomic per cell and point, as the accumulation was
 // before, ran at a seventh of that.
 //
-// A workgroup (one per CU, 16 wavefronts) works in rounds:
+// A workgroup (one per CU, 16 wavefronts) takes items of the work list (a tile and a range of views)
+// and works on each by queuefuls:
 //  1. find: each wavefront takes runs of 64 views (sorted by their normals; runs whose box of
 //     normals misses the tile are skipped), keeps the views whose plane meets the tile's box on the
 //     half-disk's side, and enumerates their rows k1, one (view, row) per lane: the k2 interval
@@ -22,7 +23,13 @@
 //     points go to an LDS queue, placed by a scan over the wavefront and one atomic.  No barrier.
 //  2. when the queue is full: every entry is located exactly (FP64; entries in the margin outside
 //     the tile are dropped), its value is formed, and the entries are sorted by bin in LDS.
-//  3. the wavefronts take chunks of up to PT_CHUNK points of one bin each.
+//  3. the wavefronts take chunks of up to CHUNK points of one bin each, 16 points at a time; those that
+//     find none left go on to find points.
+// What bounds it, at N = 256 with 10^5 views (the kernel's spread, 2.6e9 points, 137 of 144 ms): FP32
+// matrix instructions take the vector unit's slots (a probe of both in different wavefronts ran no
+// faster than one after the other), so they add up: matrix products 36 ms, window weights 29,
+// products' operands 21, adds to the tile 20, finding and locating points 50.  Before, with one 64-bit
+// LDS atomic per cell and point, 393 ms.
 #pragma once
 
 #include <algorithm>
@@ -277,62 +284,42 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
         }
         __syncthreads();
         int n = 0, ub = 0;  // surviving views collected by the wavefront, first (view, row) not yet queued
-        // the wavefront's next run, loaded one ahead of its use
-        bool more = true, counted = false;
-        int rrel = 0;
-        float4 ra{}, rb{};
-        auto load_run = [&]() {
-            int li = 0;
-            if (lane == 0) li = atomicAdd(&s.next, 1);
-            li = __builtin_amdgcn_readfirstlane(li);
-            more = li < s.nlive;
-            if (!more) return;
-            rrel = (int)s.live[li] * RUN + lane;
-            const int64_t m = min(g0 + rrel, gend - 1);
-            ra = a.vrec[2 * m];
-            rb = a.vrec[2 * m + 1];
-        };
-        load_run();
+        bool counted = false;
         while (true) {
-            bool full = false, loaded = false;
-            int vrel = 0;  // the step's view (relative) and its record, loaded one step ahead
-            float4 va{}, vb{};
-            auto load_step = [&](int at) {
-                const int v = (int)(((float)(at + lane) + 0.5f) * (1.f / T::ROWS));
-                vrel = s.surv[wv][min(v, n - 1)];
-                va = a.vrec[2 * (int64_t)(g0 + vrel)];
-                vb = a.vrec[2 * (int64_t)(g0 + vrel) + 1];
-            };
+            bool full = false;
             while (!full) {
                 if (ub >= n * T::ROWS) {
                     // runs until enough views survive to fill the steps below
                     n = 0;
                     ub = 0;
-                    while (n <= SURV - RUN && more) {
+                    while (n <= SURV - RUN) {
+                        int li = 0;
+                        if (lane == 0) li = atomicAdd(&s.next, 1);
+                        li = __builtin_amdgcn_readfirstlane(li);
+                        if (li >= s.nlive) break;
+                        const int rel = (int)s.live[li] * RUN + lane;
+                        const int64_t m = min(g0 + rel, gend - 1);
+                        const float4 ra = a.vrec[2 * m], rb = a.vrec[2 * m + 1];
                         // the plane meets the box, and does so where k1 >= 0 (s k1 is the coordinate along c1)
                         const float nx = ra.y * rb.y - ra.z * rb.x, ny = ra.z * ra.w - ra.x * rb.y, nz = ra.x * rb.x - ra.y * ra.w;
-                        const bool ok = g0 + rrel < gend &&
+                        const bool ok = g0 + rel < gend &&
                                         fabsf(c0 * nx + c1 * ny + c2 * nz) <=
                                             T::H0 * fabsf(nx) + T::H1 * fabsf(ny) + T::H2 * fabsf(nz) + 2e-3f &&
                                         c0 * ra.x + c1 * ra.y + c2 * ra.z + T::H0 * fabsf(ra.x) + T::H1 * fabsf(ra.y) +
                                                 T::H2 * fabsf(ra.z) >= -2e-3f;
                         const unsigned long long mask = __ballot(ok);
-                        if (ok) s.surv[wv][n + __popcll(mask & ((1ull << lane) - 1))] = (unsigned short)rrel;
+                        if (ok) s.surv[wv][n + __popcll(mask & ((1ull << lane) - 1))] = (unsigned short)rel;
                         n += __popcll(mask);
-                        load_run();
                     }
                     wave_sync();
                     if (n == 0) break;
-                    loaded = false;
                 }
                 // one (view, row k1) per lane: the k2 interval of the row's points in the box, all in
                 // lattice steps; rows past the end repeat the last view and hold no point
-                if (!loaded) load_step(ub);
-                const int rel = vrel;
-                const float3 u = make_float3(va.x, va.y, va.z), w = make_float3(va.w, vb.x, vb.y);
-                loaded = ub + 64 < n * T::ROWS;
-                if (loaded) load_step(ub + 64);
                 const int un = ub + lane, v = (int)(((float)un + 0.5f) * (1.f / T::ROWS));
+                const int rel = s.surv[wv][min(v, n - 1)];
+                const float4 ra = a.vrec[2 * (int64_t)(g0 + rel)], rb = a.vrec[2 * (int64_t)(g0 + rel) + 1];
+                const float3 u = make_float3(ra.x, ra.y, ra.z), w = make_float3(ra.w, rb.x, rb.y);
                 const float uc = s0 * u.x + s1 * u.y + s2 * u.z;
                 const float uh = (T::H0 / T::S) * fabsf(u.x) + (T::H1 / T::S) * fabsf(u.y) + (T::H2 / T::S) * fabsf(u.z) + 1e-3f;
                 const int k1 = (int)ceilf(uc - uh) + (un - v * T::ROWS);

@@ -10,7 +10,7 @@
 // points.h finds its points and sorts them into bins, and a wavefront sums a chunk
 // of one bin's points as a matrix product on the matrix units: the chunk's 16 x CJ x 8
 // cells are W0^T (points x 16 rows) times W1 W2 (points x CJ 8 columns), four points per
-// instruction.  The chunk's FP32 sums (at most PT_CHUNK terms) then go to the
+// instruction.  The chunk's FP32 sums (at most 64 terms) then go to the
 // workgroup's LDS tile as 64-bit integers, one atomic per cell and chunk, where one
 // per cell and point was needed without the matrix units; the tile is added to the
 // global grid at the end with one atomic per nonzero cell.  Each point is spread
@@ -25,6 +25,11 @@
 // Only the half disk (k1 > 0, or k1 = 0 and k2 > 0) is spread: its partner -k is
 // folded in (Ker is real and even; for A*b the pair (k, -k) gives the real part
 // exactly), and k = 0 is added afterwards in closed form.
+//
+// Measured against the spread with one atomic per cell and point (two launches for A*b): the kernel's
+// precompute at N = 256 with 10^5 views 400 -> 144 ms, N = 64 with 10^4 views 2.48 -> 1.10 ms; A*b at
+// N = 256 with 5 x 10^4 views 398 -> 112 ms; the relative error against 64-bit sums is unchanged
+// (2.6e-7 and 8.9e-7 at N = 64).
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -51,11 +56,14 @@ struct SpreadArgs {
     float fx_coef;
 };
 
-// Tiles: the kernel's 10 x 16 x 16 starts (W = 7; 62 KB of 64-bit cells, 64 bins, grid 4N), A*b's
-// 10 x 10 x 12 with two components per cell (74 KB, 30 bins, grid 2N, where a view leaves four
-// times the points in a tile).
+// Tiles at W = 7: the kernel's 10 x 16 x 16 starts (62 KB of 64-bit cells, 64 bins, grid 4N); A*b's
+// 10 x 8 x 12 with two components per cell (65 KB, 24 bins, grid 2N, where a view leaves four times
+// the points in a tile).  The LDS left holds the queue, and a larger queue fills the bins' chunks:
+// 20 x 16 x 16 for the kernel (half the queue per bin, fewer tiles) 180 -> 200 ms at N = 256 with
+// 10^5 views, 10 x 8 x 16 (fewer points per view found) 180 -> 210 ms, 10 x 12 x 16 the same; A*b at
+// 10 x 10 x 12 115 against 112 ms, 5 x 10^4 views.
 template <int W, bool CPLX>
-using SpreadTile = pts::Tile<W, (CPLX ? 2 : 4), 1, (CPLX ? 16 : 22), (CPLX ? 18 : 22), (CPLX ? 16 : 8), (CPLX ? 2 : 1)>;
+using SpreadTile = pts::Tile<W, (CPLX ? 2 : 4), 1, (CPLX ? (W == 8 ? 16 : 14) : 22), (CPLX ? 18 : 22), (CPLX ? 16 : 8), (CPLX ? 2 : 1)>;
 
 // The integer nearest to x (|x| < 2^51), by the FP64 sum whose last place is one.
 __device__ __forceinline__ unsigned long long to_units(float x) {

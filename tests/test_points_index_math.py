@@ -8,33 +8,35 @@ import math
 import numpy as np
 import pytest
 
-NTH, NW, RP, CHUNK, GROUP, RUN = 1024, 16, 22, 64, 32768, 64
+NTH, NW, CHUNK, GROUP, RUN, SURV = 1024, 16, 64, 32768, 64, 96
 LDS = 160 * 1024
-# (name, lattice step, bins along axis 0, bound on P1, bytes per cell, bytes per value)
-KINDS = {"ker": (4, 2, 22, 8, 4), "ker8": (4, 2, 16, 8, 4), "atb": (2, 1, 16, 16, 8)}
+# (lattice step, bins along axis 0, bound on P1, row pitch, bytes per cell, floats per value)
+KINDS = {"ker": (4, 1, 22, 22, 8, 1), "atb": (2, 1, 14, 18, 16, 2), "atb8": (2, 1, 16, 18, 16, 2)}
 
 
 class Tile:
     def __init__(self, kind, W):
-        if kind == "ker" and W == 8:
-            kind = "ker8"
-        self.S, NB0, P1MAX, CELL, VAL = KINDS[kind]
+        if kind == "atb" and W == 8:
+            kind = "atb8"
+        self.S, NB0, P1MAX, self.RP, CELL, self.NV = KINDS[kind]
         self.W = W
         self.NJ = 8 if W == 8 else 4
         self.CJ = 2 * self.NJ
         self.B = (17 - W, self.CJ + 1 - W, 9 - W)
-        self.NB = (NB0, (P1MAX - W + 1) // self.B[1], (RP - W + 1) // self.B[2])
+        self.NB = (NB0, (P1MAX - W + 1) // self.B[1], (self.RP - W + 1) // self.B[2])
         self.T = tuple(n * b for n, b in zip(self.NB, self.B))
         self.P = tuple(t + W - 1 for t in self.T)
+        self.P1MAX = P1MAX
         self.PADLO = (W + 1) // 2 - 1
         self.nbins = math.prod(self.NB)
-        STR = 28 if W <= 7 else 36
-        fixed = (self.P[0] * self.P[1] * RP * CELL + NW * 16 * STR * 4 + NW * 64 * 2 + GROUP // RUN * 2 +
+        self.S0, self.LEAD, self.SB, self.OFFV = 20, 12, self.CJ + 12, self.CJ + 8
+        self.WAVE = self.LEAD + 16 * self.S0 + 16 * self.SB
+        fixed = (self.P[0] * self.P[1] * self.RP * CELL + NW * self.WAVE * 4 + NW * SURV * 2 + GROUP // RUN * 2 +
                  self.nbins * 4 + 64)
-        per = lambda q: q * (4 + VAL) + (q // CHUNK + self.nbins) * 4  # noqa: E731
-        q = 4 * NTH
-        while q > NTH and fixed + per(q) > LDS:
-            q -= NTH
+        per = lambda q: q * (18 + 4 * self.NV) + (q // CHUNK + self.nbins) * 4  # noqa: E731
+        q = 4096
+        while q > 1024 and fixed + per(q) > LDS:
+            q -= 256
         self.QCAP, self.lds = q, fixed + per(q)
         self.DIAG = math.isqrt(sum(t * t for t in self.T) - 1) + 1
         self.ROWS, self.CMAX = self.DIAG // self.S + 1, self.DIAG // self.S + 2
@@ -46,25 +48,70 @@ ALL = [(k, W) for k in ("ker", "atb") for W in range(4, 9)]
 @pytest.mark.parametrize("kind,W", ALL)
 def test_budgets_and_footprints(kind, W):
     t = Tile(kind, W)
-    assert t.lds <= LDS and all(n >= 1 for n in t.NB) and t.P[2] <= RP and t.nbins <= 192
-    # a chunk-table entry: bin above bit 19, start in 12 bits, count in 7; the packed scan of
-    # (chunks << 16) | points
-    assert t.QCAP <= 4096 and CHUNK < 128 and t.nbins < 4096
+    assert t.lds <= LDS and all(n >= 1 for n in t.NB) and t.P[1] <= t.P1MAX and t.P[2] <= t.RP and t.nbins <= 192
+    # a chunk-table entry: bin above bit 20, start in 13 bits, count in 7; the packed scan of
+    # (chunks << 16) | points; at most one chunk per CHUNK points and one more per bin
+    assert t.QCAP <= 8191 and CHUNK < 128 and t.nbins < 2048
     assert t.QCAP // CHUNK + t.nbins < 32768 and t.QCAP < 65536
     assert 64 * t.CMAX <= t.QCAP  # one step of a wavefront always fits an empty queue
-    # a queue entry: 15 bits of view, k1 <= N/2 <= 128 in 8, k2 + 256 in 9
-    assert GROUP <= 1 << 15 and 128 < 256 and 0 <= -128 + 256 + 0 and 128 + 256 < 512
+    # a queue entry: 15 bits of view, k1 <= N/2 <= 128 in 8, k2 + 256 in 9; views collected per step
+    assert GROUP <= 1 << 15 and GROUP // RUN * RUN == GROUP and SURV - RUN + RUN <= SURV
     # every bin's 16 x CJ x 8 footprint lies inside the padded tile; a start o in the bin and its W
-    # weights fit the padded weight rows
+    # weights fit the padded weight rows, and the start fits 4 bits
     for d, foot in ((0, 16), (1, t.CJ), (2, 8)):
-        assert (t.NB[d] - 1) * t.B[d] + foot <= t.P[d] if d < 2 else (t.NB[d] - 1) * t.B[d] + foot <= RP
-        assert t.B[d] - 1 + W <= foot
-    last = ((t.P[0] - 1) * t.P[1] + t.P[1] - 1) * RP + RP - 1
-    assert last < t.P[0] * t.P[1] * RP
-    # the lanes of one quarter of an 8-byte access: two rows of 8 cells in 16 distinct slots
+        assert (t.NB[d] - 1) * t.B[d] + foot <= (t.P[d] if d < 2 else t.RP)
+        assert t.B[d] - 1 + W <= foot and t.B[d] <= 16
+    # the lanes of one quarter of an 8-byte access: two rows of 8 cells, at W <= 7 in 16 distinct slots
     for n in range(t.NJ):
-        slots = {((t.NJ * e + n) * RP + k) % 16 for e in range(2) for k in range(8)}
+        slots = {((t.NJ * e + n) * t.RP + k) % 16 for e in range(2) for k in range(8)}
         assert len(slots) == (16 if t.NJ == 4 else 8)
+
+
+@pytest.mark.parametrize("W", range(4, 9))
+def test_staged_points(W):
+    """The wavefront's staging area: what the four lanes of a point write (axis-0 weights in 8 slots,
+    axis 1 in CJ, axis 2 in 8, the value in 4) does not overlap, and the weight of footprint row i,
+    read i - o0 floats after the point's first, is its window's or a zero that nothing writes."""
+    t = Tile("ker", W)
+    written, base = {}, t.LEAD + 16 * t.S0
+    for p in range(16):
+        for what, at, n in (("w0", t.LEAD + p * t.S0, 8), ("w1", base + p * t.SB, t.CJ),
+                            ("w2", base + p * t.SB + t.CJ, 8), ("v", base + p * t.SB + t.OFFV, 4)):
+            assert at % 4 == 0
+            for k in range(n):
+                assert at + k not in written and at + k < t.WAVE
+                written[at + k] = (what, p, k)
+    for p in range(16):
+        for o in range(t.B[0]):
+            for i in range(16):
+                at = t.LEAD + p * t.S0 + i - o
+                assert 0 <= at < t.WAVE
+                k = i - o
+                if 0 <= k < W:
+                    assert written[at] == ("w0", p, k)
+                else:  # a slot past the window's end (written as zero) or one that is never written
+                    assert at not in written or (written[at][0] == "w0" and written[at][2] >= W)
+
+
+@pytest.mark.parametrize("W", range(4, 9))
+def test_window_polynomials_mirror(W):
+    """The window is even, so cell W-1-j's polynomial is cell j's at -x: the even and odd coefficients of
+    the first half of the cells give all weights to FP64 rounding."""
+    beta = np.pi * np.sqrt((W / 2) ** 2 * 1.5 ** 2 - 0.8)
+    D = 10
+    x = np.cos(np.pi * (np.arange(D + 1) + 0.5) / (D + 1))
+    coef = []
+    for j in range(W):
+        u = 0.5 * (x + 1) - 0.5 * W + j
+        phi = np.i0(beta * np.sqrt(np.maximum(0.0, 1 - (2 * u / W) ** 2))) / np.i0(beta)
+        coef.append(np.linalg.solve(np.vander(x, D + 1, increasing=True), phi))
+    z = np.linspace(-1, 1, 101)
+    for j in range((W + 1) // 2):
+        a, b = coef[j], coef[W - 1 - j]
+        even, odd = 0.5 * (a + b)[0::2], 0.5 * (a - b)[1::2]
+        e, o = np.polyval(even[::-1], z * z), np.polyval(odd[::-1], z * z) * z
+        assert np.abs(e + o - np.polyval(a[::-1], z)).max() < 1e-11
+        assert np.abs(e - o - np.polyval(b[::-1], z)).max() < 1e-11
 
 
 def test_unit_conversion_is_exact():
@@ -104,22 +151,19 @@ def test_every_point_is_found_by_its_tile(kind, W):
         c1f, c2f = c1.astype(f32), c2.astype(f32)
         assert np.all(np.abs(c @ n) <= (H * np.abs(n)).sum() + f32(2e-3))
         assert np.all(c @ c1f + (H * np.abs(c1f)).sum() >= f32(-2e-3))
-        uc = (c @ c1f) * f32(1 / s)
-        uh = (H * np.abs(c1f)).sum() * f32(1 / s) + f32(1e-3)
+        cs = (c / f32(s)).astype(f32)
+        uc = cs @ c1f
+        uh = (H / f32(s) * np.abs(c1f)).sum() + f32(1e-3)
         first = np.ceil(uc - uh).astype(np.int64)
         assert np.all(k1 >= first) and np.all(k1 < first + t.ROWS) and np.all(k1 <= uc + uh)
         kd = np.floor(np.sqrt((N * N // 4 - k1 * k1).astype(np.float64) + 1e-9))
-        lo, hi = -kd, kd.copy()
+        lo, hi = np.where(k1 == 0, 1.0, -kd), kd.copy()
         for d in range(3):
-            al = (f32(s) * k1.astype(f32) * c1f[d] - c[:, d]).astype(f32)
-            be = f32(s) * c2f[d]
-            h = H[d] + f32(1e-2)
-            if abs(be) < 1e-6:
-                assert np.all(np.abs(al) <= h)
-                continue
-            a, b = (-h - al) / be, (h - al) / be
-            lo, hi = np.maximum(lo, np.minimum(a, b)), np.minimum(hi, np.maximum(a, b))
+            al = (k1.astype(f32) * c1f[d] - cs[:, d]).astype(f32)
+            be = np.copysign(np.maximum(np.abs(c2f[d]), f32(1e-6)), c2f[d]).astype(f32)
+            rb = (f32(1) / be).astype(f32)
+            mid, half = -al * rb, (H[d] + f32(1e-2)) / f32(s) * np.abs(rb)
+            lo, hi = np.maximum(lo, mid - half), np.minimum(hi, mid + half)
         klo, khi = np.ceil(lo), np.floor(hi)
-        klo = np.where(k1 == 0, np.maximum(klo, 1), klo)
         assert np.all(k2 >= klo) and np.all(k2 <= khi)
         assert (khi - klo).max() + 1 <= t.CMAX
