@@ -229,17 +229,31 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
 }
 
 // bits of the largest |component| of n complex values (atomic max on the bits of non-negative
-// floats, which order like the floats); *out starts at 0
-__global__ void k_absmax(const float4* __restrict__ b, int64_t n2, const float2* __restrict__ tail, int ntail,
-                         unsigned* out) {
+// floats, which order like the floats); *out starts at 0.  HBM-bound (20.6 GB in 4.3 ms); one atomic
+// per workgroup and at most 2,048 of them: with one per wavefront of up to 65,536 workgroups the
+// atomics on the one word took 2.8 ms, whatever the size (N = 64 with 9,973 views: 2.84 -> 0.07 ms).
+__global__ void __launch_bounds__(256) k_absmax(const float4* __restrict__ b, int64_t n2, const float2* __restrict__ tail,
+                                                int ntail, unsigned* out) {
+    __shared__ float red[4];
     float m = 0.f;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n2; i += (int64_t)gridDim.x * blockDim.x) {
-        const float4 v = b[i];
+    const int64_t step = (int64_t)gridDim.x * 256;
+    auto take = [&](const float4& v) {
         m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    };
+    int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    for (; i + 3 * step < n2; i += 4 * step) {
+        const float4 v0 = b[i], v1 = b[i + step], v2 = b[i + 2 * step], v3 = b[i + 3 * step];
+        take(v0);
+        take(v1);
+        take(v2);
+        take(v3);
     }
+    for (; i < n2; i += step) take(b[i]);
     if (blockIdx.x == 0 && (int)threadIdx.x < ntail) m = fmaxf(m, fmaxf(fabsf(tail[threadIdx.x].x), fabsf(tail[threadIdx.x].y)));
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, __float_as_uint(m));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(out, __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
 }
 
 __global__ void k_set_u32(unsigned* p, unsigned v) { *p = v; }
@@ -249,13 +263,15 @@ __global__ void k_fill_zero(float4* p, size_t n4) {
         p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// Re sum_m h_m(0) b(0, m): the k = 0 term of Re A*b (its exponential is 1 for all n).
-__global__ void k_atb_k0(const float2* __restrict__ b, const int32_t* group, const float* table, int Q, int M,
-                         int P, double* out) {
+// Re sum_m h_m(0) b(0, m): the k = 0 term of Re A*b (its exponential is 1 for all n).  Each view's
+// sample lies in a line of its own, so the sum waits on memory: block j of the grid sums every
+// gridDim.x-th run of 256 views into out[j] (one block for 5 x 10^4 views took 268 us).
+__global__ void __launch_bounds__(256) k_atb_k0(const float2* __restrict__ b, const int32_t* group, const float* table,
+                                                int Q, int M, int P, double* out) {
     __shared__ double red[4];
     double acc = 0.0;
     const int c = (P - 1) / 2;
-    for (int m = threadIdx.x; m < M; m += 256) {
+    for (int m = blockIdx.x * 256 + threadIdx.x; m < M; m += gridDim.x * 256) {
         const int g = group ? group[m] : 0;
         const float h = table ? table[(int64_t)g * Q] : 1.f;
         acc += (double)h * (double)b[(int64_t)m * P + c].x;
@@ -263,7 +279,14 @@ __global__ void k_atb_k0(const float2* __restrict__ b, const int32_t* group, con
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) out[0] = red[0] + red[1] + red[2] + red[3];
+    if (threadIdx.x == 0) out[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
+// out[0] = the sum of n <= 64 partial sums (one wavefront)
+__global__ void k_sum64(const double* __restrict__ part, int n, double* out) {
+    double v = (int)threadIdx.x < n ? part[threadIdx.x] : 0.0;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if (threadIdx.x == 0) out[0] = v;
 }
 
 // chalf[p1][p2][n3] (n3 in [0, N)) -> kerc[p1][p2][p3] using Ker(-n) = Ker(n); p3 = N is 0.
@@ -420,7 +443,7 @@ hipError_t spread_atb(firm_plan p, const float2* b, float2* grid) {
     // the fixed-point unit follows from the largest |component| of b, found first
     const int64_t n = (int64_t)p->M * p->P;
     hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, p->stream, p->fx_bmax, 0u);
-    hipLaunchKernelGGL(k_absmax, dim3(grid_blocks(n / 2)), dim3(256), 0, p->stream,
+    hipLaunchKernelGGL(k_absmax, dim3(std::max(1, std::min(grid_blocks(n / 2), 2048))), dim3(256), 0, p->stream,
                        reinterpret_cast<const float4*>(b), n / 2, b + (n / 2) * 2, (int)(n % 2), p->fx_bmax);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -428,7 +451,10 @@ hipError_t spread_atb(firm_plan p, const float2* b, float2* grid) {
 }
 
 hipError_t atb_k0_term(firm_plan p, const float2* b, double* out) {
-    hipLaunchKernelGGL(k_atb_k0, dim3(1), dim3(256), 0, p->stream, b, p->group, p->table, p->Q, p->M, p->P, out);
+    const int nb = std::min(64, (p->M + 1023) / 1024);
+    hipLaunchKernelGGL(k_atb_k0, dim3(nb), dim3(256), 0, p->stream, b, p->group, p->table, p->Q, p->M, p->P,
+                       nb == 1 ? out : p->partials);
+    if (nb > 1) hipLaunchKernelGGL(k_sum64, dim3(1), dim3(64), 0, p->stream, p->partials, nb, out);
     return hipGetLastError();
 }
 
