@@ -357,9 +357,9 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
         e = std::min(std::max(e, -100), 100);
         p->fx_ker = std::ldexp(1.0f, e);
     }
-    std::vector<int> wk = spread_points_worklist(N, p->kbw, M, false);
-    std::vector<int> wa = spread_points_worklist(N, p->kbw, M, true);
-    std::vector<int> wp = spread_worklist(2 * N, TileDims{PJ_TILE, PJ_TILE, PJ_TILE}, 2 * N - 1, 0.0, M, SP_VBLK);
+    std::vector<int> wk = spread_worklist(N, p->kbw, M, false);
+    std::vector<int> wa = spread_worklist(N, p->kbw, M, true);
+    std::vector<int> wp = project_worklist(N, p->kbw, M);
     p->ntiles_ker = (int)(wk.size() / 4);
     p->ntiles_atb = (int)(wa.size() / 4);
     p->ntiles_prj = (int)(wp.size() / 4);

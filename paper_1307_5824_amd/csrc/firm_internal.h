@@ -167,6 +167,7 @@ int fft_apply_cg_step_partials(firm_plan p);
 int fft_apply_cg_partials(firm_plan p);
 
 // ---- spread.hip ----
+hipError_t set_word(int* p, int v, hipStream_t s);  // *p = v on the device
 hipError_t spread_ker(firm_plan p, float* grid);
 hipError_t spread_atb(firm_plan p, const float2* b, float2* grid);
 hipError_t atb_k0_term(firm_plan p, const float2* b, double* out);
@@ -214,9 +215,9 @@ firm_status cg_solve64(firm_plan p, const double* atb, double* x, double lam, do
 hipError_t precond_set(firm_plan p, const float* d_centred);
 
 struct TileDims { int t0, t1, t2; };
-std::vector<int> spread_worklist(int L, TileDims T, int last, double shift, int M, int gran);
-std::vector<int> spread_points_worklist(int N, int W, int M, bool cplx);
-constexpr int PJ_TILE = 12;   // the forward projector's tile edge
+std::vector<int> points_worklist(int L, TileDims T, int W, int M);
+std::vector<int> spread_worklist(int N, int W, int M, bool cplx);
+std::vector<int> project_worklist(int N, int W, int M);
 constexpr int SP_VRUN = 64;   // views per run of the gridding's view order (one wavefront's)
 constexpr int SP_VBLK = 512;  // views per block of the gridding's view order (its workgroup size)
 void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, std::vector<float>& datb);

@@ -45,7 +45,7 @@ constexpr int CHUNK = 64;     // points of one bin that a wavefront takes at a t
 constexpr int GROUP = 32768;  // views per group: a queue entry holds 15 bits of view, 8 of k1, 9 of k2
 constexpr int RUN = SP_VRUN;  // views per run (with one box of normals)
 constexpr int SURV = 96;      // surviving views that a wavefront collects before it enumerates rows
-constexpr int LDS_MAX = 160 * 1024;
+constexpr int LDS_MAX = 160 * 1024 - 640;  // 640 bytes are the kernels' own (the disk's row starts)
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -64,10 +64,11 @@ struct Args {
 // Geometry of the tiles of window width W.  NB0: bins along axis 0; P1MAX: bound on the padded extent
 // of axis 1; RP: pitch of a tile row in cells, 4 RP = 8 (mod 16), so that the two rows of 8 cells,
 // four rows apart, that the lanes of one quarter of an 8-byte access hit at W <= 7 share no bank;
-// CELL: bytes per cell of the kernel's LDS tile; NV: floats of a queued value.
-template <int W_, int S_, int NB0_, int P1MAX, int RP_, int CELL, int NV_>
+// CELL: bytes per cell of the kernel's LDS tile; NV: floats of a queued value, or of a result (GATHER_).
+template <int W_, int S_, int NB0_, int P1MAX, int RP_, int CELL, int NV_, bool GATHER_ = false>
 struct Tile {
     static constexpr int W = W_, S = S_, RP = RP_, NV = NV_;  // S: grid cells per lattice step
+    static constexpr bool GATHER = GATHER_;
     static constexpr int NJ = W == 8 ? 8 : 4, CJ = 2 * NJ;
     static constexpr int B0 = 17 - W, B1 = CJ + 1 - W, B2 = 9 - W;
     static constexpr int NB0 = NB0_, NB1 = (P1MAX - W + 1) / B1, NB2 = (RP - W + 1) / B2, NB = NB0 * NB1 * NB2;
@@ -83,7 +84,7 @@ struct Tile {
     static constexpr int WAVE = LEAD + 16 * S0 + 16 * SB;
     static_assert(B0 - 1 <= LEAD && S0 - (B0 - 1) >= 8 && S0 >= 16, "zeros on both sides of the window");
     static constexpr int LDS_FIXED = CELLS * CELL + NW * WAVE * 4 + NW * SURV * 2 + (GROUP / RUN) * 2 + NB * 4 + 64;
-    static constexpr int lds_of(int q) { return LDS_FIXED + q * (18 + 4 * NV) + (q / CHUNK + NB) * 4; }
+    static constexpr int lds_of(int q) { return LDS_FIXED + q * (20 + 4 * NV) + (q / CHUNK + NB) * 4; }
     static constexpr int queue_cap() {
         int q = 4096;
         while (q > 1024 && lds_of(q) > LDS_MAX) q -= 256;
@@ -103,9 +104,9 @@ struct Tile {
 template <class T>
 struct Lds {
     int queue[T::QCAP];           // found points, in the order found
-    float f[3 + T::NV][T::QCAP];  // sorted points: the offsets f of their first cells along axes 0, 1, 2
-                                  // and their values
+    float f[3 + T::NV][T::QCAP];  // their offsets f of the first cells along axes 0, 1, 2 and their values
     unsigned short off[T::QCAP];  // their starts in the bin, 4 bits per axis
+    unsigned short order[T::QCAP];  // the points by bin
     alignas(16) float wave[NW][T::WAVE];
     int ctab[T::NCT];
     int hist[T::NB];
@@ -185,7 +186,7 @@ struct Point {
 template <class T>
 __device__ __forceinline__ Point<T> load_point(const Lds<T>& s, int at, int cnt) {
     const int lane = threadIdx.x & 63, p = lane >> 2;
-    const int i = at + min(p, cnt - 1);
+    const int i = s.order[at + min(p, cnt - 1)];
     const bool zero = (lane & 3) == 3 && p >= cnt;
     Point<T> x;
     const float f = (&s.f[0][0])[(lane & 3) * T::QCAP + i];
@@ -251,12 +252,14 @@ __device__ __forceinline__ void for_items(const Args& a, Lds<T>& s, F&& item) {
 
 // Runs over the points of the tile whose first window starts (in the shifted count) are t0, t1, t2.
 // Per queueful, `fetch(view, k1, k2)` loads what an entry's value needs and `value(loaded, k1, k2, v)`
-// forms it; then the wavefronts take chunks of one bin's points: `open(bin)`, per round of 16 staged
-// points `round(points, position)`, `close(bin)`.  `begin()` runs once, by all threads, before the
-// first queueful.
-template <class T, class FB, class FL, class FV, class FO, class FR, class FC>
+// forms it; then the wavefronts take chunks of one bin's points: `state = open(bin)`, per round of 16
+// staged points `round(state, points, position)`, `close(state, bin)`.  `begin()` runs once, by all threads, before the
+// first queueful.  A gather has no values (NV = 2 floats hold a point's result, which `round` stores at
+// order[position]): when every chunk of a queueful is done, `finish(first view, entries, places)` takes
+// each thread's entries, entry j at tid + j NTH (place -1: none).
+template <class T, class FB, class FL, class FV, class FO, class FR, class FC, class FF>
 __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, int t0, int t1, int t2, FB&& begin,
-                                           FL&& fetch, FV&& value, FO&& open, FR&& round, FC&& close) {
+                                           FL&& fetch, FV&& value, FO&& open, FR&& round, FC&& close, FF&& finish) {
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     float* const wave = s.wave[wv];
     // the box of the tile's positions, relative to the grid's centre: starts are floor(tau + HW)
@@ -283,6 +286,8 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
             if (dmin <= lim && dmax >= -lim) s.live[atomicAdd(&s.nlive, 1)] = (unsigned short)r;
         }
         __syncthreads();
+        int ent[T::EPT], place[T::EPT];  // the thread's entries of the queueful and their sorted positions
+        bool held = false;               // a queueful whose results have not been taken
         int n = 0, ub = 0;  // surviving views collected by the wavefront, first (view, row) not yet queued
         bool counted = false;
         while (true) {
@@ -369,42 +374,61 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
             __syncthreads();
             const int nq = min(s.qn, s.qfail);
             const bool last = s.ndone == NW;
+            if (T::GATHER && held) finish(g0, ent, place);
+            held = nq > 0;
             if (nq > 0) {
                 if (!s.any) begin();
-                // exact place of every entry, its bin and its rank in the bin (bin << 16 | rank; -1: not a
-                // point of this tile).  The loads of all of a thread's entries are issued before the first
-                // is used.
-                int ent[T::EPT], place[T::EPT], starts[T::EPT];
-                float fr[T::EPT][3];
-                double c[T::EPT][6];
-                decltype(fetch(0, 0, 0)) raw[T::EPT];
+                // exact place of every entry: its offsets, starts and value (by queue position), its bin and
+                // its rank in the bin (place: bin << 16 | rank; -1: not a point of this tile).  A thread's
+                // entries go one by one, the next one's loads issued before the current one is used: all of
+                // their registers at once spill.
+                struct Entry {
+                    int e;
+                    double c[6];
+                    decltype(fetch(0, 0, 0)) raw;
+                };
+                auto load = [&](int j) {
+                    Entry x;
+                    x.e = s.queue[min(tid + j * NTH, nq - 1)];
+                    const int m = g0 + entry_view(x.e);
+#pragma unroll
+                    for (int d = 0; d < 6; ++d) x.c[d] = a.c12[6 * (int64_t)m + d];
+                    x.raw = fetch(m, entry_k1(x.e), entry_k2(x.e));
+                    return x;
+                };
+                Entry cur = load(0);
+#pragma unroll
+                for (int j = 0; j < T::EPT; ++j) place[j] = -1;
 #pragma unroll
                 for (int j = 0; j < T::EPT; ++j) {
-                    ent[j] = s.queue[min(tid + j * NTH, nq - 1)];
-                    const int m = g0 + entry_view(ent[j]);
-#pragma unroll
-                    for (int d = 0; d < 6; ++d) c[j][d] = a.c12[6 * (int64_t)m + d];
-                    raw[j] = fetch(m, entry_k1(ent[j]), entry_k2(ent[j]));
-                }
-#pragma unroll
-                for (int j = 0; j < T::EPT; ++j) {
-                    const int k1 = entry_k1(ent[j]), k2 = entry_k2(ent[j]);
+                    if (j * NTH + wv * 64 >= nq) break;  // nothing for this wavefront
+                    const Entry y = cur;
+                    if (j + 1 < T::EPT) cur = load(j + 1);
+                    const int i = tid + j * NTH, k1 = entry_k1(y.e), k2 = entry_k2(y.e);
                     int x[3];
+                    float f[3];
 #pragma unroll
                     for (int d = 0; d < 3; ++d) {
-                        const double left = left_of(T::S, T::W, k1, k2, c[j][d], c[j][3 + d], a.L), fl = floor(left);
+                        const double left = left_of(T::S, T::W, k1, k2, y.c[d], y.c[3 + d], a.L), fl = floor(left);
                         x[d] = (int)fl + 1 + T::PADLO - (d == 0 ? t0 : (d == 1 ? t1 : t2));
-                        fr[j][d] = (float)(fl + 1.0 - left);  // in (0, 1]
+                        f[d] = (float)(fl + 1.0 - left);  // in (0, 1]
                     }
-                    const bool in = tid + j * NTH < nq && (unsigned)x[0] < (unsigned)T::T0 &&
-                                    (unsigned)x[1] < (unsigned)T::T1 && (unsigned)x[2] < (unsigned)T::T2;
                     const unsigned b0 = T::NB0 == 1 ? 0u : (unsigned)x[0] / T::B0, b1 = (unsigned)x[1] / T::B1,
                                    b2 = (unsigned)x[2] / T::B2;
-                    starts[j] = (int)((x[0] - b0 * T::B0) | (x[1] - b1 * T::B1) << 4 | (x[2] - b2 * T::B2) << 8);
-                    place[j] = -1;
-                    if (in) {
+                    if (T::GATHER) ent[j] = y.e;
+                    if (i < nq && (unsigned)x[0] < (unsigned)T::T0 && (unsigned)x[1] < (unsigned)T::T1 &&
+                        (unsigned)x[2] < (unsigned)T::T2) {
                         const int bin = (int)((b0 * T::NB1 + b1) * T::NB2 + b2);
                         place[j] = (bin << 16) | atomicAdd(&s.hist[bin], 1);
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) s.f[d][i] = f[d];
+                        s.off[i] = (unsigned short)((x[0] - b0 * T::B0) | (x[1] - b1 * T::B1) << 4 | (x[2] - b2 * T::B2) << 8);
+                        if constexpr (!T::GATHER) {
+                            float val[2];
+                            value(y.raw, k1, k2, val);
+#pragma unroll
+                            for (int d = 0; d < T::NV; ++d) s.f[3 + d][i] = val[d];
+                        }
                     }
                 }
                 __syncthreads();
@@ -435,16 +459,8 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
                 __syncthreads();
 #pragma unroll
                 for (int j = 0; j < T::EPT; ++j)
-                    if (place[j] >= 0) {
-                        const int at = s.hist[place[j] >> 16] + (place[j] & 0xffff);
-                        float val[2];
-                        value(raw[j], entry_k1(ent[j]), entry_k2(ent[j]), val);
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) s.f[d][at] = fr[j][d];
-#pragma unroll
-                        for (int d = 0; d < T::NV; ++d) s.f[3 + d][at] = val[d];
-                        s.off[at] = (unsigned short)starts[j];
-                    }
+                    if (place[j] >= 0)
+                        s.order[s.hist[place[j] >> 16] + (place[j] & 0xffff)] = (unsigned short)(tid + j * NTH);
                 __syncthreads();
                 for (int b = tid; b < T::NB; b += NTH) s.hist[b] = 0;
                 // the chunks, handed out one at a time, and no barrier after them: a wavefront that finds none
@@ -465,26 +481,30 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
                 bool have = next();
                 Point<T> x{};
                 if (have) x = load_point<T>(s, at, cnt);
-                int r0 = 0;
                 while (have) {
-                    if (r0 == 0) open(bin);
-                    stage<T>(a, x, wave);
-                    const int rat = at + r0, rn = cnt - r0, rbin = bin;
-                    r0 += 16;
-                    const bool end = r0 >= cnt;
-                    if (end) {
-                        have = next();
-                        r0 = 0;
+                    // the chunk's registers live here only: held across the queueful they would spill
+                    const int cbin = bin, cat = at, ccnt = cnt;
+                    auto st = open(cbin);
+                    for (int r0 = 0;; r0 += 16) {
+                        stage<T>(a, x, wave);
+                        const bool end = r0 + 16 >= ccnt;
+                        if (!end) {
+                            x = load_point<T>(s, cat + r0 + 16, ccnt - r0 - 16);
+                        } else {
+                            have = next();
+                            if (have) x = load_point<T>(s, at, cnt);
+                        }
+                        round(st, ccnt - r0, cat + r0);
+                        wave_sync();
+                        if (end) break;
                     }
-                    if (have) x = load_point<T>(s, at + r0, cnt - r0);
-                    round(rn, rat);
-                    wave_sync();
-                    if (end) close(rbin);
+                    close(st, cbin);
                 }
             }
             if (last) break;
         }
         __syncthreads();
+        if (T::GATHER && held) finish(g0, ent, place);
         if (tid == 0) { s.nlive = 0; s.next = 0; s.ndone = 0; }
         __syncthreads();
     }

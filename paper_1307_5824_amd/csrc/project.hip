@@ -9,56 +9,39 @@
 //   1. u(n) = V(n) / phihat(n1) phihat(n2) phihat(n3)      (the window's transform)
 //   2. G(g) = sum_n u(n) exp(-2 pi i <n, g> / L), g in [0, L)^3 (three FFT passes; real u,
 //      so only q3 in [0, N] is formed, the rest is conj G(-g))
-//   3. b = sum over the W^3 window cells of weight * G(cell), one thread per sample point.
-// Step 3 walks the grid in T^3 tiles, the transpose of the gridding spread: a workgroup loads
-// its (T + W)^3 padded tile of G into LDS once, finds the sample points whose cell lies in
-// the tile (plane test, then the disk points near the plane), and each thread gathers one
-// point's W^3 window from LDS.  Every point belongs to exactly one tile, so every output is
-// written once, with no atomics.  The half disk (k1 > 0, or k1 = 0 and k2 > 0) is gathered;
-// b(-k) = conj b(k) for real V, and b(0) = h(0) sum V is formed exactly.
+//   3. b = sum over the W^3 window cells of weight * G(cell).
+// Step 3 walks the grid in tiles, the transpose of the gridding spread: a workgroup loads its padded
+// tile of G into LDS once, points.h finds the tile's points and sorts them into bins, and a wavefront
+// takes 16 points of a bin at a time: their axis-0 weights (16 points x 16 rows) times the bin's cells
+// (16 rows x CJ 8 columns, held in registers for the chunk) on the matrix units, then the weighted sum
+// over the columns.  Every point belongs to exactly one tile, so every output is written once, with
+// no atomics.  The half disk (k1 > 0, or k1 = 0 and k2 > 0) is gathered; b(-k) = conj b(k) for
+// real V, and b(0) = h(0) sum V is formed exactly.
+//
+// What bounds it and what it replaced: PROJECT_FIGURES
 #include <algorithm>
 #include <cmath>
 
 #include "firm_internal.h"
+#include "points.h"
 
-#define KB_DEG 10
-#define PJ_QCAP 2048
-#define PJ_THREADS 512
 #define PJ_PREP_BLOCKS 1024
-#define PJ_VPT 2
 
 namespace {
 
 struct ProjArgs {
-    int N, M, L, nt, P, Q, QP;
-    double s;
-    // per-view arrays in the order of the views' normals (blocks of 512 views with the box of
-    // their normals in vbox), and the map from that order to the caller's
-    const double* c12;
-    const float* nrm;
-    const int32_t* group;
-    const int* vorder;
-    const float4* vbox;
+    pts::Args p;
+    int P, Q, QP;
     const float* table;
-    const float* poly;
-    const int4* work;
     const float2* X;       // [q1][q2][q3], q3 in [0, N], pitch QP
     const double* shifts;
     const int* rowstart;
     float2* b;
 };
 
+// Tiles on the 2N grid: 10 x 16 x 16 window starts at W = 7 (62 KB of complex cells, 64 bins).
 template <int W>
-__device__ __forceinline__ void kb_weights(const float* __restrict__ poly, float x, float* out) {
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        const float* c = poly + j * (KB_DEG + 1);
-        float v = c[KB_DEG];
-#pragma unroll
-        for (int d = KB_DEG - 1; d >= 0; --d) v = fmaf(v, x, c[d]);
-        out[j] = v;
-    }
-}
+using ProjTile = pts::Tile<W, 2, 1, 22, 22, 8, 2, true>;
 
 // u = V / (phihat(n1) phihat(n2) phihat(n3)) and per-block FP64 partial sums of V.
 __global__ void __launch_bounds__(256) k_fp_prep(const float* __restrict__ V, const float* __restrict__ dec, int N,
@@ -118,293 +101,162 @@ __device__ __forceinline__ float2 grid_value(const float2* __restrict__ X, int L
     }
 }
 
-// Fine-grid position of the disk point (k1, k2) of a view along axis d, in the form the
-// gridding spread uses: the point enumeration (which tile owns a point) and the gather (where
-// its window starts) evaluate this one expression, so the two agree to the last bit.
-__device__ __forceinline__ double tau_of(double s, int k1, int k2, double cd, double c3d, double halfL) {
-    return fma(s, fma((double)k2, c3d, (double)k1 * cd), halfL);
+// Sum over each row of 16 lanes, in every lane.
+template <int CTRL>
+__device__ __forceinline__ float dpp_sum(float v) {
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_sum(float v) {
+    v = dpp_sum<0xB1>(v);     // lane ^ 1
+    v = dpp_sum<0x4E>(v);     // lane ^ 2
+    v = dpp_sum<0x141>(v);    // mirrored in 8
+    return dpp_sum<0x140>(v);  // mirrored in 16
 }
 
-// One queued point: view m and disk point (k1, k2) of the half disk.
-template <int T, int W>
-__device__ __forceinline__ void gather_point(const ProjArgs& a, const float2* __restrict__ tile, const int* tt, int m,
-                                             int k1, int k2) {
-    constexpr int PT = T + W;
-    constexpr int PADLO = (W + 1) / 2 - 1;
-    const int N = a.N;
-    const double halfL = 0.5 * a.L;
-    const double* c = a.c12 + 6 * (int64_t)m;
-    float ph[3][W];
-    int lo[3];
+template <int W>
+__global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_project(ProjArgs a) {
+    using T = ProjTile<W>;
+    constexpr int NJ = T::NJ;
+    __shared__ float2 tile[T::CELLS];
+    __shared__ pts::Lds<T> s;
+    __shared__ int rowstart[132];  // the disk's rows k1 >= 0 (N <= 256)
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int L = a.p.L, N = a.p.N;
+    const double inv_n = 1.0 / N;
+    for (int i = tid; i <= N / 2; i += pts::NTH) rowstart[i] = a.rowstart[i + N / 2];
+
+    // Lane roles: as an operand's row, point lane & 15; as its inner index and the accumulators' rows,
+    // q = lane / 16 (cell rows 4 ks + q; points 4 q + r); as columns, (axis 1, axis 2) = (NJ e + n, kk).
+    const int q = lane >> 4, e = (lane >> 3) & 1, kk = lane & 7;
+    const float* const wave = s.wave[tid >> 6];
+    const float* const rowb = wave + T::LEAD + 16 * T::S0;
+    struct Cells {
+        float2 g[4][4];       // the bin's cells of this lane (W <= 7)
+        const float2* first;  // the first of them
+    };
+    auto open = [&](int bin) {
+        Cells c;
+        const int o0 = bin / (T::NB1 * T::NB2) * T::B0, o1 = bin / T::NB2 % T::NB1 * T::B1, o2 = bin % T::NB2 * T::B2;
+        c.first = tile + ((o0 + q) * T::P1 + o1 + NJ * e) * T::RP + o2 + kk;
+        if constexpr (NJ == 4) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        // window start and weights exactly as the gridding spread forms them
-        const double tau = fmin(fmax(tau_of(a.s, k1, k2, c[d], c[3 + d], halfL), 0.0), (double)a.L);
-        const double left = tau - 0.5 * W;
-        const int b0 = (int)floor(left) + 1;
-        const float f = (float)((double)b0 - left);  // in (0, 1]
-        kb_weights<W>(a.poly, 2.f * f - 1.f, ph[d]);
-        lo[d] = min(max(b0 - (tt[d] * T - PADLO), 0), PT - W);
-    }
-    // one window plane per iteration (W^2 LDS loads in flight); the plane weight rotates
-    // through w0 so that no register array is indexed at run time
-    float ar = 0.f, ai = 0.f;
-    float w0[W];
+            for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int t = 0; t < W; ++t) w0[t] = ph[0][t];
-    const float2* pl = tile + (lo[0] * PT + lo[1]) * PT + lo[2];
-#pragma unroll 1
-    for (int j0 = 0; j0 < W; ++j0, pl += PT * PT) {
-        const float wp = w0[0];
-#pragma unroll
-        for (int t = 0; t < W - 1; ++t) w0[t] = w0[t + 1];
-#pragma unroll
-        for (int j1 = 0; j1 < W; ++j1) {
-            const float2* row = pl + j1 * PT;
-            float sr = 0.f, si = 0.f;
-#pragma unroll
-            for (int j2 = 0; j2 < W; ++j2) {
-                const float2 g = row[j2];
-                sr = fmaf(ph[2][j2], g.x, sr);
-                si = fmaf(ph[2][j2], g.y, si);
-            }
-            const float w = wp * ph[1][j1];
-            ar = fmaf(w, sr, ar);
-            ai = fmaf(w, si, ai);
-            // at most half a plane of loads in flight: keeps the gather within 128 registers
-            if (j1 == W / 2) __builtin_amdgcn_sched_barrier(0);
+                for (int n = 0; n < 4; ++n) c.g[ks][n] = c.first[(4 * ks * T::P1 + n) * T::RP];
         }
-    }
-    const int g = a.group ? a.group[m] : 0;
-    const float h = a.table ? a.table[(int64_t)g * a.Q + k1 * k1 + k2 * k2] : 1.f;
-    float cs = 1.f, sn = 0.f;
-    if (a.shifts) {
-        // theta = 2 pi x, x = <k, s_m> / N reduced to [-1/2, 1/2] in FP64, then an FP32 sincospi
-        const double x = (k1 * a.shifts[2 * (int64_t)m] + k2 * a.shifts[2 * (int64_t)m + 1]) / N;
-        sincospif(2.f * (float)(x - rint(x)), &sn, &cs);
-    }
-    // h exp(-i theta) (ar + i ai), and its conjugate at -k
-    const float2 v = make_float2(h * (ar * cs + ai * sn), h * (ai * cs - ar * sn));
-    const int idx = a.rowstart[k1 + N / 2] + k2;
-    const int64_t mo = a.vorder[m];  // the caller's view index
-    a.b[mo * a.P + idx] = v;
-    a.b[mo * a.P + (a.P - 1 - idx)] = make_float2(v.x, -v.y);
+        return c;
+    };
+    auto round = [&](const Cells& c, int cnt, int at) {
+        const int pr = lane & 15;
+        const int o = __float_as_int(rowb[pr * T::SB + T::OFFV + 1]);
+        float w0[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            w0[ks] = *reinterpret_cast<const float*>(
+                reinterpret_cast<const char*>(wave + T::LEAD + pr * T::S0 + 4 * ks + q) + o);
+        float re[4] = {0.f, 0.f, 0.f, 0.f}, im[4] = {0.f, 0.f, 0.f, 0.f};
+        auto columns = [&](const pts::f4& cr, const pts::f4& ci, int n) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float w = rowb[(4 * q + r) * T::SB + NJ * e + n];
+                re[r] = fmaf(w, cr[r], re[r]);
+                im[r] = fmaf(w, ci[r], im[r]);
+            }
+        };
+        if constexpr (NJ == 4) {
+            pts::f4 cr[4], ci[4];
+#pragma unroll
+            for (int n = 0; n < 4; ++n) cr[n] = ci[n] = pts::f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    cr[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], c.g[ks][n].x, cr[n], 0, 0, 0);
+                    ci[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], c.g[ks][n].y, ci[n], 0, 0, 0);
+                }
+#pragma unroll
+            for (int n = 0; n < 4; ++n) columns(cr[n], ci[n], n);
+        } else {
+#pragma unroll 2
+            for (int n = 0; n < NJ; ++n) {
+                pts::f4 cr = {0.f, 0.f, 0.f, 0.f}, ci = cr;
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    const float2 v = c.first[(4 * ks * T::P1 + n) * T::RP];
+                    cr = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], v.x, cr, 0, 0, 0);
+                    ci = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], v.y, ci, 0, 0, 0);
+                }
+                columns(cr, ci, n);
+            }
+        }
+        float sr = 0.f, si = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float w2 = rowb[(4 * q + r) * T::SB + T::CJ + kk];
+            const float x = row_sum(w2 * re[r]), y = row_sum(w2 * im[r]);
+            sr = (lane & 3) == r ? x : sr;
+            si = (lane & 3) == r ? y : si;
+        }
+        const int p = 4 * q + (lane & 3);
+        if ((lane & 15) < 4 && p < cnt) {
+            const int i = s.order[at + p];
+            s.f[3][i] = sr;
+            s.f[4][i] = si;
+        }
+    };
+    // the points' outputs, in the order they were found (neighbours along a row together)
+    auto finish = [&](int g0, const int* ent, const int* place) {
+#pragma unroll
+        for (int j = 0; j < T::EPT; ++j) {
+            if (place[j] < 0) continue;
+            const int64_t m = g0 + pts::entry_view(ent[j]);
+            const int k1 = pts::entry_k1(ent[j]), k2 = pts::entry_k2(ent[j]);
+            const float4 rec = a.p.vrec[2 * m + 1];  // (.., group, the caller's view)
+            const float h = a.table ? a.table[(int64_t)__float_as_int(rec.z) * a.Q + k1 * k1 + k2 * k2] : 1.f;
+            const double s1 = a.shifts ? a.shifts[2 * m] : 0.0, s2 = a.shifts ? a.shifts[2 * m + 1] : 0.0;
+            const float ar = s.f[3][tid + j * pts::NTH], ai = s.f[4][tid + j * pts::NTH];
+            float cs = 1.f, sn = 0.f;
+            if (a.shifts) {
+                // theta = 2 pi x, x = <k, s_m> / N (N a power of 2) reduced to [-1/2, 1/2] in FP64, then an
+                // FP32 sincospi
+                const double x = (k1 * s1 + k2 * s2) * inv_n;
+                sincospif(2.f * (float)(x - rint(x)), &sn, &cs);
+            }
+            // h exp(-i theta) (ar + i ai), and its conjugate at -k
+            const float2 v = make_float2(h * (ar * cs + ai * sn), h * (ai * cs - ar * sn));
+            const int idx = rowstart[k1] + k2;
+            const int64_t mo = (int64_t)__float_as_int(rec.w) * a.P;
+            a.b[mo + idx] = v;
+            a.b[mo + (a.P - 1 - idx)] = make_float2(v.x, -v.y);
+        }
+    };
+    pts::for_items<T>(a.p, s, [&](int4 wk) {
+        const int nt12 = a.p.nt1 * a.p.nt2;
+        const int t0 = wk.x / nt12 * T::T0, t1 = wk.x / a.p.nt2 % a.p.nt1 * T::T1, t2 = wk.x % a.p.nt2 * T::T2;
+        // the padded tile of G: LDS cell l holds grid index (t - PADLO + l - L/2) mod L (a power of 2)
+        auto begin = [&]() {
+            for (int i = tid; i < T::P0 * T::P1 * T::P2; i += pts::NTH) {
+                const int l0 = i / (T::P1 * T::P2), l1 = i / T::P2 % T::P1, l2 = i % T::P2;
+                const int q0 = (t0 - T::PADLO + l0 - L / 2) & (L - 1), q1 = (t1 - T::PADLO + l1 - L / 2) & (L - 1),
+                          q2 = (t2 - T::PADLO + l2 - L / 2) & (L - 1);
+                tile[(l0 * T::P1 + l1) * T::RP + l2] = grid_value(a.X, L, N, a.QP, q0, q1, q2);
+            }
+        };
+        pts::for_points<T>(a.p, s, wk, t0, t1, t2, begin, [](int, int, int) { return 0; },
+                           [](int, int, int, float*) {}, open, round, [](const Cells&, int) {}, finish);
+    });
 }
 
-// Four waves per SIMD (two 512-thread workgroups per CU) up to W = 7; the W = 8 gather needs
-// more than 128 registers and runs at two.
-template <int T, int W, int NTH>
-__global__ void __launch_bounds__(NTH, (W <= 7 ? 4 : 2)) k_project(ProjArgs a) {
-    constexpr int PT = T + W;                  // padded tile edge (window starts in [0, T])
-    constexpr int PADLO = (W + 1) / 2 - 1;
-    constexpr int NCELL = PT * PT * PT;
-    constexpr int IMGCAP = (PJ_VPT + 1) * NTH;
-    __shared__ float2 tile[NCELL];
-    __shared__ int img_m[IMGCAP], img_r[IMGCAP];  // surviving views and their first candidate row
-    // queued points (view slot, k1, k2), -1 for an unused entry
-    __shared__ int queue[PJ_QCAP];
-    __shared__ int nimg, qn;
-
-    const int tid = threadIdx.x;
-    const int4 wk = a.work[blockIdx.x];
-    const int nt = a.nt;
-    const int tt[3] = {wk.x / (nt * nt), (wk.x / nt) % nt, wk.x % nt};
-    const int L = a.L, N = a.N;
-    const double halfL = 0.5 * L;
-
-    // the padded tile of G: LDS cell l holds grid index (tt * T - PADLO + l - L/2) mod L
-    const int o0 = tt[0] * T - PADLO - L / 2, o1 = tt[1] * T - PADLO - L / 2, o2 = tt[2] * T - PADLO - L / 2;
-    for (int i = tid; i < NCELL; i += NTH) {
-        const int l0 = i / (PT * PT), l1 = (i / PT) % PT, l2 = i % PT;
-        const int q0 = ((o0 + l0) % L + L) % L, q1 = ((o1 + l1) % L + L) % L, q2 = ((o2 + l2) % L + L) % L;
-        tile[i] = grid_value(a.X, L, N, a.QP, q0, q1, q2);
-    }
-    // The tile's constants, the same in every lane, kept in LDS and read where they are used
-    // (vector registers holding them across the loops below would spill): its centre relative to
-    // the grid's centre in FP32 (the plane test's margin of 2e-3 and the candidate rows' slack
-    // of one row are far above its rounding), the row radius rk, and the slab bounds: positions
-    // tau whose (clamped) cell lies in the tile, widened by a margin far above the rounding of the
-    // FP32 row intervals; the edge tiles also own the clamped cells beyond the grid.  Each
-    // interval is then trimmed to the exact one with the FP64 cell test.
-    __shared__ float tcl[3], blo[3], bhi[3], rkl;
-    if (tid == 0) {
-        qn = 0;
-        nimg = 0;
-        constexpr float MARGIN = 1e-2f, FAR = 1e30f;
-        for (int d = 0; d < 3; ++d) {
-            tcl[d] = tt[d] * T + 0.5f * T - 0.5f * L;
-            blo[d] = tt[d] == 0 ? -FAR : tt[d] * T - MARGIN;
-            bhi[d] = (tt[d] + 1) * T >= L ? FAR : (tt[d] + 1) * T + MARGIN;
-        }
-        rkl = (T * 0.8660254f + 1e-3f) / (float)a.s;
-    }
-    const int S = (int)floorf(2.f * ((T * 0.8660254f + 1e-3f) / (float)a.s)) + 3;  // candidate rows per view
-    const int N2 = N * N;
-    // the point (k1, k2) of the view with columns c lies in the tile: inside the disk and its
-    // clamped cell in the tile per axis
-    auto in_tile = [&](const double* c, int k1, int k2) {
-        if (4 * (k1 * k1 + k2 * k2) > N2) return false;
-        bool in = true;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            int cell = (int)floor(tau_of(a.s, k1, k2, c[d], c[3 + d], halfL));
-            cell = cell < 0 ? 0 : (cell > L - 1 ? L - 1 : cell);
-            in = in && (cell / T == tt[d]);
-        }
-        return in;
-    };
-
-    auto flush = [&](int n) {
-        for (int qi = tid; qi < n; qi += NTH) {
-            const int e = queue[qi];
-            if (e >= 0) gather_point<T, W>(a, tile, tt, img_m[e >> 17], (e >> 9) & 255, (e & 511) - 256);
-        }
-    };
-
-    // blocks of NTH views (the work range starts on a block), up to NTH of them at a time: their
-    // boxes of normals are tested first, into a bit mask, and the rounds below visit the live
-    // blocks only, PJ_VPT at a time (a block whose box of normals n gives no |n . c| within the
-    // bound below for the tile's centre c holds no view that meets the tile)
-    __shared__ unsigned bmask[NTH / 32];
-    __shared__ int lblk[PJ_VPT + 2];  // a round's live blocks (in the group), their count, the cursor
-    const int blk0 = wk.y / NTH, blk1 = (wk.z + NTH - 1) / NTH;
-    for (int gb = blk0; gb < blk1; gb += NTH) {
-        if (tid < NTH / 32) bmask[tid] = 0u;
-        __syncthreads();
-        if (gb + tid < blk1) {
-            const float4 lo = a.vbox[2 * (gb + tid)], hi = a.vbox[2 * (gb + tid) + 1];
-            const float p0 = tcl[0] * lo.x, q0 = tcl[0] * hi.x, p1 = tcl[1] * lo.y, q1 = tcl[1] * hi.y;
-            const float p2 = tcl[2] * lo.z, q2 = tcl[2] * hi.z;
-            const float dmin = fminf(p0, q0) + fminf(p1, q1) + fminf(p2, q2);
-            const float dmax = fmaxf(p0, q0) + fmaxf(p1, q1) + fmaxf(p2, q2);
-            const float lim = 0.5f * T * lo.w + 3e-3f;
-            if (dmin <= lim && dmax >= -lim) atomicOr(&bmask[tid >> 5], 1u << (tid & 31));
-        }
-        if (tid == 0) lblk[PJ_VPT + 1] = 0;
-        bool more = true;  // uniform
-        while (more) {
-            __syncthreads();  // the counters are reset, the tile and the block mask are in place
-            // 1. views whose plane meets the tile, at least NTH of them (or all that remain),
-            //    PJ_VPT live blocks per round, one view per thread and block, so that the loads
-            //    of a round overlap
-            int ni = 0;
-            while (true) {
-                if (tid == 0) {
-                    int n = 0, cur = lblk[PJ_VPT + 1];
-                    while (n < PJ_VPT && cur < NTH) {
-                        const unsigned w = bmask[cur >> 5] & (~0u << (cur & 31));
-                        if (w == 0u) {
-                            cur = (cur | 31) + 1;
-                            continue;
-                        }
-                        const int b = (cur & ~31) + __builtin_ctz(w);
-                        lblk[n++] = b;
-                        cur = b + 1;
-                    }
-                    lblk[PJ_VPT] = n;
-                    lblk[PJ_VPT + 1] = cur;
-                }
-                __syncthreads();
-                const int nl = lblk[PJ_VPT];
-                if (nl == 0) {
-                    more = false;
-                    ni = nimg;
-                    break;
-                }
-                float4 nv[PJ_VPT];
-                unsigned livev = 0u;
-#pragma unroll
-                for (int v = 0; v < PJ_VPT; ++v) {
-                    const int m = v < nl ? (gb + lblk[v]) * NTH + tid : wk.z;
-                    const bool live = m < wk.z;
-                    nv[v] = live ? *reinterpret_cast<const float4*>(a.nrm + 4 * (int64_t)m) : make_float4(0.f, 0.f, 0.f, 0.f);
-                    livev |= (unsigned)live << v;
-                }
-#pragma unroll
-                for (int v = 0; v < PJ_VPT; ++v) {
-                    const int m = v < nl ? (gb + lblk[v]) * NTH + tid : wk.z;
-                    // the plane meets the tile's cube: distance of the centre at most the cube's
-                    // half extent along the normal
-                    const float dist = fabsf(tcl[0] * nv[v].x + tcl[1] * nv[v].y + tcl[2] * nv[v].z);
-                    if (((livev >> v) & 1u) && dist <= 0.5f * T * (fabsf(nv[v].x) + fabsf(nv[v].y) + fabsf(nv[v].z)) + 2e-3f) {
-                        const double* c = a.c12 + 6 * (int64_t)m;
-                        const float u1 = (tcl[0] * (float)c[0] + tcl[1] * (float)c[1] + tcl[2] * (float)c[2]) / (float)a.s;
-                        const int sl = atomicAdd(&nimg, 1);
-                        img_m[sl] = m;
-                        img_r[sl] = (int)ceilf(u1 - rkl) - 1;
-                    }
-                }
-                __syncthreads();
-                ni = nimg;
-                __syncthreads();  // read by every thread before the next round adds to it
-                if (ni >= NTH) break;
-            }
-            // 2. one (view, row k1) per thread: the k2 interval whose cells lie in the tile (three
-            //    slabs, plus the disk and half-disk bounds), trimmed to the exact cell test at both
-            //    ends (the cell along a row is monotone in k2, so the points that pass form an
-            //    interval).  Queue space is reserved per thread; a reservation that does not fit
-            //    is retried after the full queue has been gathered.
-            const int units = ni * S;
-            for (int base = 0; base < units; base += NTH) {
-                const int u = base + tid;
-                int sl = 0, k1 = 0, klo = 0, cnt = 0;
-                if (u < units) {
-                    sl = u / S;
-                    k1 = img_r[sl] + (u - sl * S);
-                    if (k1 >= 0 && 4 * k1 * k1 <= N2) {
-                        const double* c = a.c12 + 6 * (int64_t)img_m[sl];
-                        const int kd = (int)sqrtf((float)(N2 / 4 - k1 * k1)) + 1;  // >= the disk's |k2|
-                        float lo = (float)-kd, hi = (float)kd;
-                        bool ok = true;
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) {
-                            const float al = (float)(a.s * k1 * c[d] + halfL), be = (float)(a.s * c[3 + d]);
-                            if (fabsf(be) < 1e-6f) {
-                                ok = ok && al >= blo[d] && al <= bhi[d];
-                            } else {
-                                // reciprocal to about 1 ulp: far inside the bounds' margin
-                                const float rb = __builtin_amdgcn_rcpf(be);
-                                const float t1 = (blo[d] - al) * rb, t2 = (bhi[d] - al) * rb;
-                                lo = fmaxf(lo, fminf(t1, t2));
-                                hi = fminf(hi, fmaxf(t1, t2));
-                            }
-                        }
-                        klo = (int)ceilf(lo);
-                        if (k1 == 0) klo = max(klo, 1);
-                        int khi = (int)floorf(hi);
-                        if (ok) {
-                            while (klo <= khi && !in_tile(c, k1, klo)) ++klo;
-                            while (khi >= klo && !in_tile(c, k1, khi)) --khi;
-                            // a row crosses a tile in at most T sqrt(3) / s + 1 points
-                            cnt = min(khi - klo + 1, 32);
-                        }
-                    }
-                }
-                bool pend = cnt > 0;
-                while (true) {
-                    if (pend) {
-                        const int pos = atomicAdd(&qn, cnt);
-                        if (pos + cnt <= PJ_QCAP) {
-                            for (int j = 0; j < cnt; ++j) queue[pos + j] = (sl << 17) | (k1 << 9) | (klo + j + 256);
-                            pend = false;
-                        } else {
-                            for (int j = pos; j < PJ_QCAP; ++j) queue[j] = -1;
-                        }
-                    }
-                    if (!__syncthreads_or(pend)) break;
-                    flush(PJ_QCAP);  // the queue is full
-                    __syncthreads();
-                    if (tid == 0) qn = 0;
-                    __syncthreads();
-                }
-            }
-            // 3. the view slots are refilled next round: gather what is queued
-            const int nq = qn;  // every reservation of the last chunk fitted (read after its barrier)
-            flush(nq);
-            __syncthreads();
-            if (tid == 0) { qn = 0; nimg = 0; }
-        }
-    }
+template <int W>
+hipError_t launch_w(firm_plan p, ProjArgs& a) {
+    using T = ProjTile<W>;
+    a.p.nt1 = (a.p.L + T::T1) / T::T1;  // starts 0 .. L
+    a.p.nt2 = (a.p.L + T::T2) / T::T2;
+    hipError_t e = set_word(p->taken, 0, p->stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_project<W>), dim3(std::min(a.p.nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -425,22 +277,27 @@ hipError_t forward_project(firm_plan p, const float* V, float2* b) {
     if ((e = fft_project_grid(p, p->tmp, p->T1, reinterpret_cast<float2*>(p->ws1), X)) != hipSuccess) return e;
     if (p->ntiles_prj == 0) return hipSuccess;
     ProjArgs a;
-    a.N = N; a.M = p->M; a.L = L; a.nt = (L + PJ_TILE - 1) / PJ_TILE; a.P = p->P; a.Q = p->Q; a.QP = p->QP;
-    a.s = 2.0;
-    // the views in the order of their normals (blocks of SP_VBLK views, one per round and thread)
-    static_assert(PJ_THREADS == SP_VBLK, "a block of views per round and thread");
-    a.c12 = p->c12s; a.nrm = p->nrms; a.group = p->groups; a.table = p->table; a.poly = p->kb_poly;
-    a.vorder = p->vorder; a.vbox = p->vbox;
-    a.work = reinterpret_cast<const int4*>(p->tiles_prj);
-    a.X = X; a.shifts = p->shiftss; a.rowstart = p->rowstart; a.b = b;
-    const dim3 grid(p->ntiles_prj), blk(PJ_THREADS);
+    a.p = point_args(p, L, p->tiles_prj, p->ntiles_prj);
+    a.P = p->P; a.Q = p->Q; a.QP = p->QP;
+    a.table = p->table; a.X = X; a.shifts = p->shiftss; a.rowstart = p->rowstart; a.b = b;
     switch (p->kbw) {
-        case 4: hipLaunchKernelGGL((k_project<PJ_TILE, 4, PJ_THREADS>), grid, blk, 0, st, a); break;
-        case 5: hipLaunchKernelGGL((k_project<PJ_TILE, 5, PJ_THREADS>), grid, blk, 0, st, a); break;
-        case 6: hipLaunchKernelGGL((k_project<PJ_TILE, 6, PJ_THREADS>), grid, blk, 0, st, a); break;
-        case 7: hipLaunchKernelGGL((k_project<PJ_TILE, 7, PJ_THREADS>), grid, blk, 0, st, a); break;
-        case 8: hipLaunchKernelGGL((k_project<PJ_TILE, 8, PJ_THREADS>), grid, blk, 0, st, a); break;
+        case 4: return launch_w<4>(p, a);
+        case 5: return launch_w<5>(p, a);
+        case 6: return launch_w<6>(p, a);
+        case 7: return launch_w<7>(p, a);
+        case 8: return launch_w<8>(p, a);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+}
+
+std::vector<int> project_worklist(int N, int W, int M) {
+    TileDims d;
+    switch (W) {
+        case 4: d = tile_dims<ProjTile<4>>(); break;
+        case 5: d = tile_dims<ProjTile<5>>(); break;
+        case 6: d = tile_dims<ProjTile<6>>(); break;
+        case 7: d = tile_dims<ProjTile<7>>(); break;
+        default: d = tile_dims<ProjTile<8>>(); break;
+    }
+    return points_worklist(2 * N, d, W, M);
 }

@@ -144,17 +144,21 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
     // A lane's part of the 16 x CJ x 8 footprint: columns (axis 1, axis 2) = (NJ e + n, kk), rows
     // (axis 0) 4 q + r of accumulator register r; as an operand, point q of the four, row lane & 15.
     const int q = lane >> 4, e = (lane >> 3) & 1, kk = lane & 7;
-    pts::f4 acc[NC][NJ];
+    struct Sums {
+        pts::f4 acc[NC][NJ];
+    };
     auto open = [&](int) {
+        Sums x;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int n = 0; n < NJ; ++n) acc[c][n] = pts::f4{0.f, 0.f, 0.f, 0.f};
+            for (int n = 0; n < NJ; ++n) x.acc[c][n] = pts::f4{0.f, 0.f, 0.f, 0.f};
+        return x;
     };
     const float* const wave = s.wave[tid >> 6];
     const float* const row0 = wave + T::LEAD + q * T::S0 + (lane & 15);
     const float* const rowb = wave + T::LEAD + 16 * T::S0 + q * T::SB;
-    auto round = [&](int cnt, int) {
+    auto round = [&](Sums& x, int cnt, int) {
         // the operands of KB steps (four points each) are read together, then used
         constexpr int KB = NJ == 4 ? 4 : 1;
 #pragma unroll
@@ -187,12 +191,12 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
                     const float w12 = w1[j][n] * w2[j];
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
-                        acc[c][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[c], w12, acc[c][n], 0, 0, 0);
+                        x.acc[c][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[c], w12, x.acc[c][n], 0, 0, 0);
                 }
             }
         }
     };
-    auto close = [&](int bin) {
+    auto close = [&](const Sums& x, int bin) {
         const int o0 = bin / (T::NB1 * T::NB2) * T::B0, o1 = bin / T::NB2 % T::NB1 * T::B1, o2 = bin % T::NB2 * T::B2;
         const int cell = ((o0 + 4 * q) * T::P1 + o1 + NJ * e) * T::RP + o2 + kk;
 #pragma unroll
@@ -201,22 +205,22 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
             for (int n = 0; n < NJ; ++n)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    __hip_atomic_fetch_add(&tile[c][cell + (r * T::P1 + n) * T::RP], to_units(acc[c][n][r]),
+                    __hip_atomic_fetch_add(&tile[c][cell + (r * T::P1 + n) * T::RP], to_units(x.acc[c][n][r]),
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     const int L = a.p.L;
     pts::for_items<T>(a.p, s, [&](int4 wk) {
         const int nt12 = a.p.nt1 * a.p.nt2;
         const int t0 = wk.x / nt12 * T::T0, t1 = wk.x / a.p.nt2 % a.p.nt1 * T::T1, t2 = wk.x % a.p.nt2 * T::T2;
-        pts::for_points<T>(a.p, s, wk, t0, t1, t2, begin, fetch, value, open, round, close);
+        pts::for_points<T>(a.p, s, wk, t0, t1, t2, begin, fetch, value, open, round, close, [](int, int*, int*) {});
         if (!s.any) return;
         for (int i = tid; i < T::P0 * T::P1 * T::P2; i += pts::NTH) {
             const int l0 = i / (T::P1 * T::P2), l1 = i / T::P2 % T::P1, l2 = i % T::P2;
             const int li = (l0 * T::P1 + l1) * T::RP + l2;
-            // grid index = position mod L, position = cell - L/2
-            const int g0 = ((t0 - T::PADLO + l0 - L / 2) % L + L) % L;
-            const int g1 = ((t1 - T::PADLO + l1 - L / 2) % L + L) % L;
-            const int g2 = ((t2 - T::PADLO + l2 - L / 2) % L + L) % L;
+            // grid index = position mod L (a power of 2), position = cell - L/2
+            const int g0 = (t0 - T::PADLO + l0 - L / 2) & (L - 1);
+            const int g1 = (t1 - T::PADLO + l1 - L / 2) & (L - 1);
+            const int g2 = (t2 - T::PADLO + l2 - L / 2) & (L - 1);
             const int64_t gi = ((int64_t)g0 * L + g1) * L + g2;
             // the integer sum, rounded once to FP32
 #pragma unroll
@@ -335,7 +339,8 @@ hipError_t launch_w(firm_plan p, SpreadArgs& a, int nwork) {
     using T = SpreadTile<W, CPLX>;
     a.p.nt1 = (a.p.L + T::T1) / T::T1;  // starts 0 .. L
     a.p.nt2 = (a.p.L + T::T2) / T::T2;
-    hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, p->stream, reinterpret_cast<unsigned*>(a.p.taken), 0u);
+    hipError_t e = set_word(p->taken, 0, p->stream);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_spread<W, CPLX>), dim3(std::min(nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
     return hipGetLastError();
 }
@@ -373,15 +378,17 @@ TileDims spread_dims(int W) {
 
 }  // namespace
 
-// Host work list: tiles of T0 x T1 x T2 cells of an L^3 grid that can hold points, each split
-// into view ranges, ordered by expected work (tiles near the origin meet every view's plane) so
-// that the heavy ones start first.  The ranges hold about 1 / SP_ITEMS of all expected (tile, view)
-// meetings: the tiles at the origin meet every view, and one workgroup for up to 16,384 views left
-// them running alone (A*b at N = 64 with 9,973 views: 21.9 -> 9.1 ms).  `last`: the last
-// cell that a tile may own (L - 1, or L for window starts); `shift`: the position of cell 0's lower
-// edge; ranges start on multiples of `gran` views.
+// Host work list: tiles of window starts (0 .. L; at odd widths start 0 lies half a cell below
+// position 0) that can hold points, each split into view ranges, ordered by expected work (tiles near
+// the origin meet every view's plane) so that the heavy ones start first.  The ranges hold about
+// 1 / SP_ITEMS of all expected (tile, view) meetings: the tiles at the origin meet every view, and
+// one workgroup for up to 16,384 views left them running alone (A*b at N = 64 with 9,973 views: 21.9 ->
+// 9.1 ms with the atomic spread).
 #define SP_ITEMS 2048
-std::vector<int> spread_worklist(int L, TileDims T, int last, double shift, int M, int gran) {
+std::vector<int> points_worklist(int L, TileDims T, int W, int M) {
+    constexpr int gran = 4 * SP_VRUN;  // ranges are whole runs of views
+    const double shift = W % 2 ? -0.5 : 0.0;
+    const int last = L;
     const int T0 = T.t0, T1 = T.t1, T2 = T.t2;
     const int n0 = last / T0 + 1, n1 = last / T1 + 1, n2 = last / T2 + 1;
     const double Rt = 0.5 * std::sqrt((double)T0 * T0 + (double)T1 * T1 + (double)T2 * T2);
@@ -417,11 +424,9 @@ std::vector<int> spread_worklist(int L, TileDims T, int last, double shift, int 
     return out;
 }
 
-// The work lists of the kernel's spread (cplx = false, grid 4N) and A*b's (grid 2N): tiles of window
-// starts 0 .. L, whose first one lies half a cell below zero for odd widths.
-std::vector<int> spread_points_worklist(int N, int W, int M, bool cplx) {
-    const int L = (cplx ? 2 : 4) * N;
-    return spread_worklist(L, cplx ? spread_dims<true>(W) : spread_dims<false>(W), L, W % 2 ? -0.5 : 0.0, M, 4 * SP_VRUN);
+// The work lists of the kernel's spread (cplx = false, grid 4N) and A*b's (grid 2N).
+std::vector<int> spread_worklist(int N, int W, int M, bool cplx) {
+    return points_worklist((cplx ? 2 : 4) * N, cplx ? spread_dims<true>(W) : spread_dims<false>(W), W, M);
 }
 
 hipError_t fill_zero(void* ptr, size_t bytes, hipStream_t s) {
@@ -432,6 +437,11 @@ hipError_t fill_zero(void* ptr, size_t bytes, hipStream_t s) {
         hipError_t e = hipMemsetAsync((char*)ptr + n4 * 16, 0, rem, s);
         if (e != hipSuccess) return e;
     }
+    return hipGetLastError();
+}
+
+hipError_t set_word(int* p, int v, hipStream_t s) {
+    hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, reinterpret_cast<unsigned*>(p), (unsigned)v);
     return hipGetLastError();
 }
 

@@ -9,9 +9,10 @@ import numpy as np
 import pytest
 
 NTH, NW, CHUNK, GROUP, RUN, SURV = 1024, 16, 64, 32768, 64, 96
-LDS = 160 * 1024
+LDS = 160 * 1024 - 640  # 132 row starts of the disk are the kernels' own
 # (lattice step, bins along axis 0, bound on P1, row pitch, bytes per cell, floats per value)
-KINDS = {"ker": (4, 1, 22, 22, 8, 1), "atb": (2, 1, 14, 18, 16, 2), "atb8": (2, 1, 16, 18, 16, 2)}
+KINDS = {"ker": (4, 1, 22, 22, 8, 1), "atb": (2, 1, 14, 18, 16, 2), "atb8": (2, 1, 16, 18, 16, 2),
+         "prj": (2, 1, 22, 22, 8, 2)}
 
 
 class Tile:
@@ -33,7 +34,7 @@ class Tile:
         self.WAVE = self.LEAD + 16 * self.S0 + 16 * self.SB
         fixed = (self.P[0] * self.P[1] * self.RP * CELL + NW * self.WAVE * 4 + NW * SURV * 2 + GROUP // RUN * 2 +
                  self.nbins * 4 + 64)
-        per = lambda q: q * (18 + 4 * self.NV) + (q // CHUNK + self.nbins) * 4  # noqa: E731
+        per = lambda q: q * (20 + 4 * self.NV) + (q // CHUNK + self.nbins) * 4  # noqa: E731
         q = 4096
         while q > 1024 and fixed + per(q) > LDS:
             q -= 256
@@ -42,7 +43,7 @@ class Tile:
         self.ROWS, self.CMAX = self.DIAG // self.S + 1, self.DIAG // self.S + 2
 
 
-ALL = [(k, W) for k in ("ker", "atb") for W in range(4, 9)]
+ALL = [(k, W) for k in ("ker", "atb", "prj") for W in range(4, 9)]
 
 
 @pytest.mark.parametrize("kind,W", ALL)
