@@ -152,13 +152,13 @@ const char* firm_last_error(firm_plan p) {
 
 void firm_plan_destroy(firm_plan p) {
     if (!p) return;
-    void* dev[] = {p->S2, p->c12, p->nrm, p->group, p->table, p->shifts, p->kb_poly, p->deconv_ker, p->deconv_atb,
+    void* dev[] = {p->S2, p->c12, p->group, p->table, p->shifts, p->deconv_ker, p->deconv_atb,
                    p->tw, p->kerc, p->khat, p->T1, p->T2, p->r, p->p, p->z, p->tmp, p->partials,
                    p->partials2, p->partials3, p->scal, p->dhalf, p->S1, p->grid, p->ws1, p->ws2,
                    p->tiles_ker, p->tiles_atb, p->dscal, p->rowstart, p->flags, p->khat64, p->T1d,
                    p->T2d, p->tw64, p->x64, p->r64, p->p64, p->q64, p->y64, p->atb64, p->rhs, p->dvec,
-                   p->img_ws, p->khat16, p->shtab, p->uws, p->usc, p->c12s, p->nrms, p->groups, p->shiftss,
-                   p->vorder, p->vbox, p->vrec, p->rbox, p->tiles_prj};
+                   p->img_ws, p->khat16, p->shtab, p->uws, p->usc, p->c12s, p->shiftss,
+                   p->vrec, p->rbox, p->tiles_prj};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     if (p->host_scal) (void)hipHostFree(p->host_scal);
@@ -251,15 +251,11 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     p->ker_k0 = k0;
     // The gridding visits the views in the order of their planes' normals: each normal folded to
     // the hemisphere where its largest component is positive, keyed by that axis and a Morton
-    // code of the other two components over it, so that a block of SP_VBLK consecutive views
-    // spans a small cone and the box of its normals lets a tile skip the whole block.
-    std::vector<int32_t> vord(M);
+    // code of the other two components over it, so that a run of SP_VRUN consecutive views
+    // spans a small cone and the box of its normals lets a tile skip the whole run.
     std::vector<double> c12s((size_t)M * 6);
-    std::vector<float> nrms((size_t)M * 4);
-    std::vector<int32_t> grps(M);
+    std::vector<float> nrms((size_t)M * 3);
     std::vector<double> shs(shifts ? (size_t)M * 2 : 0);
-    const int nvblk = (M + SP_VBLK - 1) / SP_VBLK;
-    std::vector<float4> vbox((size_t)nvblk * 2);
     const int nrun = (M + SP_VRUN - 1) / SP_VRUN;
     std::vector<float4> vrec((size_t)M * 2), rbox((size_t)nrun * 2);
     {
@@ -280,16 +276,13 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
         std::stable_sort(key.begin(), key.end());
         for (int j = 0; j < M; ++j) {
             const int m = key[j].second;
-            vord[j] = m;
             for (int d = 0; d < 6; ++d) c12s[6 * (size_t)j + d] = c12[6 * (size_t)m + d];
             const float* n = &nrm[4 * (size_t)m];
             int ax = 0;
             for (int d = 1; d < 3; ++d)
                 if (std::fabs(n[d]) > std::fabs(n[ax])) ax = d;
             const float sg = n[ax] < 0.f ? -1.f : 1.f;  // the same plane; the tests use |n . x|
-            for (int d = 0; d < 3; ++d) nrms[4 * (size_t)j + d] = sg * n[d];
-            nrms[4 * (size_t)j + 3] = 0.f;
-            grps[j] = grp[m];
+            for (int d = 0; d < 3; ++d) nrms[3 * (size_t)j + d] = sg * n[d];
             const double* c = &c12[6 * (size_t)m];
             auto bits = [](int32_t i) { float f; std::memcpy(&f, &i, 4); return f; };
             vrec[2 * (size_t)j] = make_float4((float)c[0], (float)c[1], (float)c[2], (float)c[3]);
@@ -300,22 +293,11 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
             float lo[3] = {1e30f, 1e30f, 1e30f}, hi[3] = {-1e30f, -1e30f, -1e30f};
             for (int j = r * SP_VRUN; j < std::min(M, (r + 1) * SP_VRUN); ++j)
                 for (int d = 0; d < 3; ++d) {
-                    lo[d] = std::min(lo[d], nrms[4 * (size_t)j + d]);
-                    hi[d] = std::max(hi[d], nrms[4 * (size_t)j + d]);
+                    lo[d] = std::min(lo[d], nrms[3 * (size_t)j + d]);
+                    hi[d] = std::max(hi[d], nrms[3 * (size_t)j + d]);
                 }
             rbox[2 * (size_t)r] = make_float4(lo[0], lo[1], lo[2], 0.f);
             rbox[2 * (size_t)r + 1] = make_float4(hi[0], hi[1], hi[2], 0.f);
-        }
-        for (int bk = 0; bk < nvblk; ++bk) {
-            float lo[3] = {1e30f, 1e30f, 1e30f}, hi[3] = {-1e30f, -1e30f, -1e30f};
-            double l1 = 0.0;
-            for (int j = bk * SP_VBLK; j < std::min(M, (bk + 1) * SP_VBLK); ++j) {
-                const float* n = &nrms[4 * (size_t)j];
-                for (int d = 0; d < 3; ++d) { lo[d] = std::min(lo[d], n[d]); hi[d] = std::max(hi[d], n[d]); }
-                l1 = std::max(l1, (double)std::fabs(n[0]) + std::fabs(n[1]) + std::fabs(n[2]));
-            }
-            vbox[2 * (size_t)bk] = make_float4(lo[0], lo[1], lo[2], (float)(l1 * (1.0 + 1e-6)));
-            vbox[2 * (size_t)bk + 1] = make_float4(hi[0], hi[1], hi[2], 0.f);
         }
     }
     std::vector<int> rowstart(N + 1);
@@ -369,19 +351,13 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     hipError_t e = hipSuccess;
     auto chk = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     chk(dalloc(&p->c12, c12.size()));
-    chk(dalloc(&p->nrm, nrm.size()));
     chk(dalloc(&p->group, (size_t)M));
     if (ctf_table) chk(dalloc(&p->table, (size_t)G * Q));
     if (shifts) chk(dalloc(&p->shifts, (size_t)M * 2));
     chk(dalloc(&p->c12s, c12s.size()));
-    chk(dalloc(&p->nrms, nrms.size()));
-    chk(dalloc(&p->groups, (size_t)M));
     if (shifts) chk(dalloc(&p->shiftss, (size_t)M * 2));
-    chk(dalloc(&p->vorder, (size_t)M));
-    chk(dalloc(&p->vbox, vbox.size()));
     chk(dalloc(&p->vrec, vrec.size()));
     chk(dalloc(&p->rbox, rbox.size()));
-    chk(dalloc(&p->kb_poly, poly.size()));
     chk(dalloc(&p->deconv_ker, dker.size()));
     chk(dalloc(&p->deconv_atb, datb.size()));
     chk(dalloc(&p->tw, (size_t)FIRM_TWN));
@@ -429,19 +405,13 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
         if (e == hipSuccess && bytes) e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
     };
     up(p->c12, c12.data(), c12.size() * sizeof(double));
-    up(p->nrm, nrm.data(), nrm.size() * sizeof(float));
     up(p->group, grp.data(), grp.size() * sizeof(int32_t));
     if (ctf_table) up(p->table, ctf_table, (size_t)G * Q * sizeof(float));
     if (shifts) up(p->shifts, shifts, (size_t)M * 2 * sizeof(double));
     up(p->c12s, c12s.data(), c12s.size() * sizeof(double));
-    up(p->nrms, nrms.data(), nrms.size() * sizeof(float));
-    up(p->groups, grps.data(), grps.size() * sizeof(int32_t));
     if (shifts) up(p->shiftss, shs.data(), shs.size() * sizeof(double));
-    up(p->vorder, vord.data(), vord.size() * sizeof(int32_t));
-    up(p->vbox, vbox.data(), vbox.size() * sizeof(float4));
     up(p->vrec, vrec.data(), vrec.size() * sizeof(float4));
     up(p->rbox, rbox.data(), rbox.size() * sizeof(float4));
-    up(p->kb_poly, poly.data(), poly.size() * sizeof(float));
     up(p->deconv_ker, dker.data(), dker.size() * sizeof(float));
     up(p->deconv_atb, datb.data(), datb.size() * sizeof(float));
     up(p->tw, tw.data(), tw.size() * sizeof(float2));

@@ -31,26 +31,20 @@ struct firm_plan_s {
 
     // geometry (device)
     double* c12 = nullptr;     // M x 6: columns 1 and 2 of R_m^{-1}
-    float* nrm = nullptr;      // M x 4: plane normal (c1 x c2), float
     int32_t* group = nullptr;  // M
     float* table = nullptr;    // G x Q (h), or null
     double* shifts = nullptr;  // M x 2 or null
-    // the same per-view arrays in the gridding's view order (normals folded to one hemisphere and
-    // sorted along a space-filling curve of their direction), its map to the caller's order, and
-    // per block of SP_VBLK views the box of the normals and the largest |n|_1
+    // the per-view arrays in the gridding's view order (normals folded to one hemisphere and sorted
+    // along a space-filling curve of their direction)
     double* c12s = nullptr;
-    float* nrms = nullptr;
-    int32_t* groups = nullptr;
     double* shiftss = nullptr;
-    int32_t* vorder = nullptr;  // gridding position -> view index
-    float4* vbox = nullptr;     // 2 per block: (min n, max |n|_1), (max n, 0)
     float4* vrec = nullptr;     // 2 per view: (c1, c2x), (c2y, c2z, group, caller's view), in FP32
     float4* rbox = nullptr;     // 2 per run of SP_VRUN views: (min n, 0), (max n, 0)
     double ker_k0 = 0.0;       // sum_m h_m(0)^2: the k = 0 term of Ker
 
-    // Kaiser-Bessel window (device)
-    float* kb_poly = nullptr;  // w x (KB_DEG+1) polynomial coefficients on f in [0, 1]
-    float kb_sym[44] = {};     // the same by pairs of cells, split into even and odd powers of 2 f - 1 (host)
+    // Kaiser-Bessel window (host): per pair of mirrored cells a polynomial in 2 f - 1, f in [0, 1] the
+    // offset in the cell, 6 even and then 5 odd coefficients
+    float kb_sym[44] = {};
     float fx_ker = 1.f;        // kernel gridding: integer units per unit (power of 2, terms < 2^31)
     float fx_atb_coef = 0.f;   // A*b gridding: units per unit times the largest |b component| may reach
     int* taken = nullptr;      // device word: work items handed out by the running gridding kernel (inside dscal)
@@ -219,7 +213,6 @@ std::vector<int> points_worklist(int L, TileDims T, int W, int M);
 std::vector<int> spread_worklist(int N, int W, int M, bool cplx);
 std::vector<int> project_worklist(int N, int W, int M);
 constexpr int SP_VRUN = 64;   // views per run of the gridding's view order (one wavefront's)
-constexpr int SP_VBLK = 512;  // views per block of the gridding's view order (its workgroup size)
 void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, std::vector<float>& datb);
 
 // block count helper

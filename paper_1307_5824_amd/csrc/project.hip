@@ -18,7 +18,10 @@
 // no atomics.  The half disk (k1 > 0, or k1 = 0 and k2 > 0) is gathered; b(-k) = conj b(k) for
 // real V, and b(0) = h(0) sum V is formed exactly.
 //
-// What bounds it and what it replaced: PROJECT_FIGURES
+// What bounds it, at N = 256 with 2 x 10^4 views (5.1e8 points, 38.3 ms; 65.4 with one thread per point
+// and 343 LDS reads each): the matrix products 13.3 ms of vector-unit time, their operands and the sums
+// over the columns about 8, window weights 5, the outputs with CTF and phase 5, finding and locating
+// points (with the FFTs) 14; timed with the parts switched off one at a time.
 #include <algorithm>
 #include <cmath>
 
@@ -39,9 +42,10 @@ struct ProjArgs {
     float2* b;
 };
 
-// Tiles on the 2N grid: 10 x 16 x 16 window starts at W = 7 (62 KB of complex cells, 64 bins).
+// Tiles on the 2N grid: 10 x 12 x 12 window starts at W = 7 (41 KB of complex cells, 36 bins; the rest
+// of the LDS is queue).  10 x 16 x 16 took 40.9 against 38.3 ms at N = 256 with 2 x 10^4 views.
 template <int W>
-using ProjTile = pts::Tile<W, 2, 1, 22, 22, 8, 2, true>;
+using ProjTile = pts::Tile<W, 2, 1, 18, 18, 8, 2, true>;
 
 // u = V / (phihat(n1) phihat(n2) phihat(n3)) and per-block FP64 partial sums of V.
 __global__ void __launch_bounds__(256) k_fp_prep(const float* __restrict__ V, const float* __restrict__ dec, int N,
@@ -156,12 +160,11 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_project(ProjArgs a
             w0[ks] = *reinterpret_cast<const float*>(
                 reinterpret_cast<const char*>(wave + T::LEAD + pr * T::S0 + 4 * ks + q) + o);
         float re[4] = {0.f, 0.f, 0.f, 0.f}, im[4] = {0.f, 0.f, 0.f, 0.f};
-        auto columns = [&](const pts::f4& cr, const pts::f4& ci, int n) {
+        auto columns = [&](const pts::f4& cr, const pts::f4& ci, const pts::f4& w) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float w = rowb[(4 * q + r) * T::SB + NJ * e + n];
-                re[r] = fmaf(w, cr[r], re[r]);
-                im[r] = fmaf(w, ci[r], im[r]);
+                re[r] = fmaf(w[r], cr[r], re[r]);
+                im[r] = fmaf(w[r], ci[r], im[r]);
             }
         };
         if constexpr (NJ == 4) {
@@ -175,8 +178,11 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_project(ProjArgs a
                     cr[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], c.g[ks][n].x, cr[n], 0, 0, 0);
                     ci[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], c.g[ks][n].y, ci[n], 0, 0, 0);
                 }
+            pts::f4 w1[4];  // axis-1 weights of the points 4 q + r
 #pragma unroll
-            for (int n = 0; n < 4; ++n) columns(cr[n], ci[n], n);
+            for (int r = 0; r < 4; ++r) w1[r] = *reinterpret_cast<const pts::f4*>(rowb + (4 * q + r) * T::SB + NJ * e);
+#pragma unroll
+            for (int n = 0; n < 4; ++n) columns(cr[n], ci[n], pts::f4{w1[0][n], w1[1][n], w1[2][n], w1[3][n]});
         } else {
 #pragma unroll 2
             for (int n = 0; n < NJ; ++n) {
@@ -187,7 +193,8 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_project(ProjArgs a
                     cr = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], v.x, cr, 0, 0, 0);
                     ci = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[ks], v.y, ci, 0, 0, 0);
                 }
-                columns(cr, ci, n);
+                const float* w = rowb + 4 * q * T::SB + NJ * e + n;
+                columns(cr, ci, pts::f4{w[0], w[T::SB], w[2 * T::SB], w[3 * T::SB]});
             }
         }
         float sr = 0.f, si = 0.f;

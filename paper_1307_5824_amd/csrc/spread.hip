@@ -27,8 +27,8 @@
 // exactly), and k = 0 is added afterwards in closed form.
 //
 // Measured against the spread with one atomic per cell and point (two launches for A*b): the kernel's
-// precompute at N = 256 with 10^5 views 400 -> 144 ms, N = 64 with 10^4 views 2.48 -> 1.10 ms; A*b at
-// N = 256 with 5 x 10^4 views 398 -> 112 ms; the relative error against 64-bit sums is unchanged
+// precompute at N = 256 with 10^5 views 400 -> 140 ms, N = 64 with 10^4 views 2.48 -> 1.03 ms; A*b at
+// N = 256 with 5 x 10^4 views 398 -> 101 ms; the relative error against 64-bit sums is unchanged
 // (2.6e-7 and 8.9e-7 at N = 64).
 #include <algorithm>
 #include <cmath>

@@ -12,7 +12,7 @@ NTH, NW, CHUNK, GROUP, RUN, SURV = 1024, 16, 64, 32768, 64, 96
 LDS = 160 * 1024 - 640  # 132 row starts of the disk are the kernels' own
 # (lattice step, bins along axis 0, bound on P1, row pitch, bytes per cell, floats per value)
 KINDS = {"ker": (4, 1, 22, 22, 8, 1), "atb": (2, 1, 14, 18, 16, 2), "atb8": (2, 1, 16, 18, 16, 2),
-         "prj": (2, 1, 22, 22, 8, 2)}
+         "prj": (2, 1, 18, 18, 8, 2)}
 
 
 class Tile:
