@@ -37,22 +37,12 @@ double bessel_i0(double x) {
     return sum;
 }
 
-// Kaiser-Bessel window phi(u) = I0(beta sqrt(1 - (2u/W)^2)) / I0(beta) on |u| <= W/2 and its
-// Fourier transform W sinh(sqrt(beta^2 - (W nu / 2)^2)) / sqrt(...) / I0(beta) (sin form past the
-// zero of the root).  beta follows Beatty, Nishimura & Pauly (2005) for oversampling 2.
+// Kaiser-Bessel window phi(u) = I0(beta sqrt(1 - (2u/W)^2)) / I0(beta) on |u| <= W/2; beta follows
+// Beatty, Nishimura & Pauly (2005) for oversampling 2.
 double kb_phi(double u, int W, double beta) {
     const double t = 2.0 * u / W;
     if (std::fabs(t) > 1.0) return 0.0;
     return bessel_i0(beta * std::sqrt(std::max(0.0, 1.0 - t * t))) / bessel_i0(beta);
-}
-
-double kb_phihat(double nu, int W, double beta) {
-    const double z2 = beta * beta - 0.25 * W * W * nu * nu;
-    double v;
-    if (z2 > 1e-12) { const double z = std::sqrt(z2); v = W * std::sinh(z) / z; }
-    else if (z2 < -1e-12) { const double z = std::sqrt(-z2); v = W * std::sin(z) / z; }
-    else v = W;
-    return v / bessel_i0(beta);
 }
 
 // Solve the (n x n) system A c = y by Gaussian elimination with partial pivoting.
@@ -112,18 +102,53 @@ void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, 
             const double a = coef[j * (D + 1) + k], b = coef[(W - 1 - j) * (D + 1) + k];
             p->kb_sym[j * (D + 1) + (k % 2 ? NE + k / 2 : k / 2)] = (float)(0.5 * (k % 2 ? a - b : a + b));
         }
+    // The transform of the window as the kernels evaluate it, with its FP32 coefficients: their rounding
+    // shifts the window's area by up to 2.5e-8 per axis, which the closed form would leave in the results
+    // as a common factor (at W = 7 half of the kernel's error against 64 bits).  Gauss-Legendre
+    // quadrature per cell, exact for degree 10 times a cosine of at most a quarter turn per cell.
+    constexpr int NG = 14;
+    double gx[NG], gw[NG];
+    for (int i = 0; i < NG; ++i) {
+        double x = std::cos(M_PI * (i + 0.75) / (NG + 0.5)), dp = 1.0;
+        for (int it = 0; it < 50; ++it) {
+            double p0 = 1.0, p1 = x;
+            for (int k = 2; k <= NG; ++k) { const double p2 = ((2 * k - 1) * x * p1 - (k - 1) * p0) / k; p0 = p1; p1 = p2; }
+            dp = NG * (x * p1 - p0) / (x * x - 1.0);
+            const double dx = p1 / dp;
+            x -= dx;
+            if (std::fabs(dx) < 1e-15) break;
+        }
+        gx[i] = x;
+        gw[i] = 2.0 / ((1.0 - x * x) * dp * dp);
+    }
+    std::vector<double> gu, gv;  // nodes u >= 0 of the even window, and weight times its value (both sides)
+    for (int j = 0; j < (W + 1) / 2; ++j)
+        for (int i = 0; i < NG; ++i) {
+            const float* c = p->kb_sym + j * (D + 1);
+            const double x = gx[i], y = x * x;
+            double e = 0.0, o = 0.0;
+            for (int k = NE - 1; k >= 0; --k) e = e * y + (double)c[k];
+            for (int k = D - NE; k >= 0; --k) o = o * y + (double)c[NE + k];
+            const bool mid = 2 * j + 1 == W;  // the middle cell is its own mirror, and even
+            gu.push_back(0.5 * (x + 1.0) - 0.5 * W + j);
+            gv.push_back((mid ? 0.5 : 1.0) * gw[i] * (mid ? e : e + x * o));
+        }
+    auto phihat = [&](double nu) {
+        double v = 0.0;
+        for (size_t i = 0; i < gu.size(); ++i) v += gv[i] * std::cos(nu * gu[i]);
+        return v;
+    };
     dker.assign(2 * N, 0.f);
-    const double Lk = 4.0 * N;
-    for (int pp = 0; pp < 2 * N; ++pp) {
-        if (pp == N) continue;
-        const int n = pp < N ? pp : pp - 2 * N;
-        dker[pp] = (float)(1.0 / kb_phihat(2.0 * M_PI * n / Lk, W, beta));
+    for (int n = 0; n < N; ++n) {
+        const float v = (float)(1.0 / phihat(2.0 * M_PI * n / (4.0 * N)));
+        dker[n] = v;
+        if (n > 0) dker[2 * N - n] = v;  // position N, the circulant's wrap, stays 0
     }
     datb.assign(N, 0.f);
-    const double La = 2.0 * N;
-    for (int i = 0; i < N; ++i) {
-        const int n = i - N / 2;
-        datb[i] = (float)(1.0 / kb_phihat(2.0 * M_PI * n / La, W, beta));
+    for (int n = 0; n <= N / 2; ++n) {
+        const float v = (float)(1.0 / phihat(2.0 * M_PI * n / (2.0 * N)));
+        if (n < N / 2) datb[N / 2 + n] = v;
+        datb[N / 2 - n] = v;
     }
 }
 
@@ -259,7 +284,9 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     const int nrun = (M + SP_VRUN - 1) / SP_VRUN;
     std::vector<float4> vrec((size_t)M * 2), rbox((size_t)nrun * 2);
     {
-        std::vector<std::pair<uint64_t, int32_t>> key(M);
+        // 22-bit keys, sorted by two counting passes
+        std::vector<uint32_t> key(M);
+        std::vector<int32_t> ord(M), ord2(M);
         for (int m = 0; m < M; ++m) {
             const float* n = &nrm[4 * (size_t)m];
             int ax = 0;
@@ -269,13 +296,20 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
             const double u = n[(ax + 1) % 3] * inv, v = n[(ax + 2) % 3] * inv;  // in [-1, 1]
             const uint32_t qu = (uint32_t)std::min(1023.0, std::max(0.0, (u + 1.0) * 511.5));
             const uint32_t qv = (uint32_t)std::min(1023.0, std::max(0.0, (v + 1.0) * 511.5));
-            uint64_t mort = 0;
-            for (int b = 0; b < 10; ++b) mort |= (uint64_t)((qu >> b) & 1u) << (2 * b) | (uint64_t)((qv >> b) & 1u) << (2 * b + 1);
-            key[m] = {((uint64_t)ax << 20) | mort, m};
+            uint32_t mort = 0;
+            for (int b = 0; b < 10; ++b) mort |= ((qu >> b) & 1u) << (2 * b) | ((qv >> b) & 1u) << (2 * b + 1);
+            key[m] = ((uint32_t)ax << 20) | mort;
+            ord2[m] = m;
         }
-        std::stable_sort(key.begin(), key.end());
+        for (int shift = 0; shift < 22; shift += 11) {
+            std::vector<int> at(2049, 0);
+            for (int m = 0; m < M; ++m) ++at[((key[m] >> shift) & 2047u) + 1];
+            for (int i = 0; i < 2048; ++i) at[i + 1] += at[i];
+            for (int j = 0; j < M; ++j) ord[at[(key[ord2[j]] >> shift) & 2047u]++] = ord2[j];
+            std::swap(ord, ord2);
+        }
         for (int j = 0; j < M; ++j) {
-            const int m = key[j].second;
+            const int m = ord2[j];
             for (int d = 0; d < 6; ++d) c12s[6 * (size_t)j + d] = c12[6 * (size_t)m + d];
             const float* n = &nrm[4 * (size_t)m];
             int ax = 0;
@@ -341,7 +375,7 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     }
     std::vector<int> wk = spread_worklist(N, p->kbw, M, false);
     std::vector<int> wa = spread_worklist(N, p->kbw, M, true);
-    std::vector<int> wp = project_worklist(N, p->kbw, M);
+    std::vector<int> wp = project_worklist(N, p->kbw, M, p->P, p->prj_wide);
     p->ntiles_ker = (int)(wk.size() / 4);
     p->ntiles_atb = (int)(wa.size() / 4);
     p->ntiles_prj = (int)(wp.size() / 4);

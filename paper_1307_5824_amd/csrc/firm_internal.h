@@ -95,6 +95,7 @@ struct firm_plan_s {
     int* tiles_ker = nullptr; int ntiles_ker = 0;   // work list for the kernel spread
     int* tiles_atb = nullptr; int ntiles_atb = 0;   // work list for the A*b spread
     int* tiles_prj = nullptr; int ntiles_prj = 0;   // work list for the forward projector
+    bool prj_wide = false;                          // its tiles are the wide ones (few points per tile)
     double* dscal = nullptr;   // small device scratch for the A*b k=0 term
     int* rowstart = nullptr;   // N+1: disk index of (k1, 0), so idx(k1, k2) = rowstart[k1 + N/2] + k2
     int* flags = nullptr;      // CG control words on device (see cg.hip)
@@ -211,7 +212,7 @@ hipError_t precond_set(firm_plan p, const float* d_centred);
 struct TileDims { int t0, t1, t2; };
 std::vector<int> points_worklist(int L, TileDims T, int W, int M);
 std::vector<int> spread_worklist(int N, int W, int M, bool cplx);
-std::vector<int> project_worklist(int N, int W, int M);
+std::vector<int> project_worklist(int N, int W, int M, int64_t P, bool& wide);
 constexpr int SP_VRUN = 64;   // views per run of the gridding's view order (one wavefront's)
 void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, std::vector<float>& datb);
 

@@ -41,7 +41,6 @@ namespace pts {
 
 constexpr int KB_DEG = 10;
 constexpr int NTH = 1024, NW = NTH / 64;
-constexpr int CHUNK = 64;     // points of one bin that a wavefront takes at a time
 constexpr int GROUP = 32768;  // views per group: a queue entry holds 15 bits of view, 8 of k1, 9 of k2
 constexpr int RUN = SP_VRUN;  // views per run (with one box of normals)
 constexpr int SURV = 96;      // surviving views that a wavefront collects before it enumerates rows
@@ -70,6 +69,7 @@ struct Tile {
     static constexpr int W = W_, S = S_, RP = RP_, NV = NV_;  // S: grid cells per lattice step
     static constexpr bool GATHER = GATHER_;
     static constexpr int NJ = W == 8 ? 8 : 4, CJ = 2 * NJ;
+    static constexpr int CHUNK = W == 8 ? 32 : 64;  // points of one bin that a wavefront takes at a time
     static constexpr int B0 = 17 - W, B1 = CJ + 1 - W, B2 = 9 - W;
     static constexpr int NB0 = NB0_, NB1 = (P1MAX - W + 1) / B1, NB2 = (RP - W + 1) / B2, NB = NB0 * NB1 * NB2;
     static constexpr int T0 = NB0 * B0, T1 = NB1 * B1, T2 = NB2 * B2;
@@ -439,13 +439,13 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
                     for (int b0 = 0; b0 < T::NB; b0 += 64) {
                         const int b = b0 + lane;
                         const int h = b < T::NB ? s.hist[b] : 0;
-                        const int x = (((h + CHUNK - 1) / CHUNK) << 16) | h;
+                        const int x = (((h + T::CHUNK - 1) / T::CHUNK) << 16) | h;
                         const int incl = wave_scan(x) + base;
                         const int ex = incl - x;
                         int at = ex & 0xffff, ci = ex >> 16;
                         if (b < T::NB) s.hist[b] = at;
-                        for (int rest = h; rest > 0; rest -= CHUNK, at += CHUNK, ++ci)
-                            s.ctab[ci] = (b << 20) | (at << 7) | min(rest, CHUNK);
+                        for (int rest = h; rest > 0; rest -= T::CHUNK, at += T::CHUNK, ++ci)
+                            s.ctab[ci] = (b << 20) | (at << 7) | min(rest, T::CHUNK);
                         base = __builtin_amdgcn_readlane(incl, 63);
                     }
                     if (lane == 0) {

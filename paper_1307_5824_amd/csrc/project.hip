@@ -24,6 +24,7 @@
 // points (with the FFTs) 14; timed with the parts switched off one at a time.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "firm_internal.h"
 #include "points.h"
@@ -42,10 +43,14 @@ struct ProjArgs {
     float2* b;
 };
 
-// Tiles on the 2N grid: 10 x 12 x 12 window starts at W = 7 (41 KB of complex cells, 36 bins; the rest
-// of the LDS is queue).  10 x 16 x 16 took 40.9 against 38.3 ms at N = 256 with 2 x 10^4 views.
-template <int W>
-using ProjTile = pts::Tile<W, 2, 1, 18, 18, 8, 2, true>;
+// Tiles on the 2N grid.  With many views 10 x 12 x 12 window starts at W = 7 (41 KB of complex cells,
+// 36 bins; the rest of the LDS is queue); with few points per tile, where each tile's fixed work
+// (its cells, the steps of one queueful) is what counts, 10 x 16 x 16 (62 KB, 64 bins, half the
+// tiles).  N = 256: 2 x 10^4 views (10^4 points per narrow tile) 38.3 ms narrow, 40.9 wide; 762
+// views (400 points) 4.5 narrow, 3.8 wide.  N = 128 with 5,000 views (5,300 points): 2.60, 2.73.
+template <int W, bool WIDE>
+using ProjTile = pts::Tile<W, 2, 1, (WIDE ? 22 : 18), (WIDE ? 22 : 18), 8, 2, true>;
+constexpr double PJ_WIDE_BELOW = 2000;  // points per narrow tile
 
 // u = V / (phihat(n1) phihat(n2) phihat(n3)) and per-block FP64 partial sums of V.
 __global__ void __launch_bounds__(256) k_fp_prep(const float* __restrict__ V, const float* __restrict__ dec, int N,
@@ -117,9 +122,9 @@ __device__ __forceinline__ float row_sum(float v) {
     return dpp_sum<0x140>(v);  // mirrored in 16
 }
 
-template <int W>
+template <int W, bool WIDE>
 __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_project(ProjArgs a) {
-    using T = ProjTile<W>;
+    using T = ProjTile<W, WIDE>;
     constexpr int NJ = T::NJ;
     __shared__ float2 tile[T::CELLS];
     __shared__ pts::Lds<T> s;
@@ -255,14 +260,14 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_project(ProjArgs a
     });
 }
 
-template <int W>
+template <int W, bool WIDE>
 hipError_t launch_w(firm_plan p, ProjArgs& a) {
-    using T = ProjTile<W>;
+    using T = ProjTile<W, WIDE>;
     a.p.nt1 = (a.p.L + T::T1) / T::T1;  // starts 0 .. L
     a.p.nt2 = (a.p.L + T::T2) / T::T2;
     hipError_t e = set_word(p->taken, 0, p->stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_project<W>), dim3(std::min(a.p.nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
+    hipLaunchKernelGGL((k_project<W, WIDE>), dim3(std::min(a.p.nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
     return hipGetLastError();
 }
 
@@ -288,23 +293,28 @@ hipError_t forward_project(firm_plan p, const float* V, float2* b) {
     a.P = p->P; a.Q = p->Q; a.QP = p->QP;
     a.table = p->table; a.X = X; a.shifts = p->shiftss; a.rowstart = p->rowstart; a.b = b;
     switch (p->kbw) {
-        case 4: return launch_w<4>(p, a);
-        case 5: return launch_w<5>(p, a);
-        case 6: return launch_w<6>(p, a);
-        case 7: return launch_w<7>(p, a);
-        case 8: return launch_w<8>(p, a);
+        case 4: return p->prj_wide ? launch_w<4, true>(p, a) : launch_w<4, false>(p, a);
+        case 5: return p->prj_wide ? launch_w<5, true>(p, a) : launch_w<5, false>(p, a);
+        case 6: return p->prj_wide ? launch_w<6, true>(p, a) : launch_w<6, false>(p, a);
+        case 7: return p->prj_wide ? launch_w<7, true>(p, a) : launch_w<7, false>(p, a);
+        case 8: return p->prj_wide ? launch_w<8, true>(p, a) : launch_w<8, false>(p, a);
         default: return hipErrorInvalidValue;
     }
 }
 
-std::vector<int> project_worklist(int N, int W, int M) {
-    TileDims d;
-    switch (W) {
-        case 4: d = tile_dims<ProjTile<4>>(); break;
-        case 5: d = tile_dims<ProjTile<5>>(); break;
-        case 6: d = tile_dims<ProjTile<6>>(); break;
-        case 7: d = tile_dims<ProjTile<7>>(); break;
-        default: d = tile_dims<ProjTile<8>>(); break;
-    }
-    return points_worklist(2 * N, d, W, M);
+std::vector<int> project_worklist(int N, int W, int M, int64_t P, bool& wide) {
+    auto dims = [&](auto wd) {
+        constexpr bool WD = decltype(wd)::value;
+        switch (W) {
+            case 4: return tile_dims<ProjTile<4, WD>>();
+            case 5: return tile_dims<ProjTile<5, WD>>();
+            case 6: return tile_dims<ProjTile<6, WD>>();
+            case 7: return tile_dims<ProjTile<7, WD>>();
+            default: return tile_dims<ProjTile<8, WD>>();
+        }
+    };
+    const TileDims d = dims(std::false_type{});
+    const double tiles = 4.0 / 3.0 * M_PI * std::pow((double)N, 3) / ((double)d.t0 * d.t1 * d.t2);  // in the ball
+    wide = 0.5 * (double)P * M < PJ_WIDE_BELOW * tiles;
+    return points_worklist(2 * N, wide ? dims(std::true_type{}) : d, W, M);
 }

@@ -28,8 +28,9 @@
 //
 // Measured against the spread with one atomic per cell and point (two launches for A*b): the kernel's
 // precompute at N = 256 with 10^5 views 400 -> 140 ms, N = 64 with 10^4 views 2.48 -> 1.03 ms; A*b at
-// N = 256 with 5 x 10^4 views 398 -> 101 ms; the relative error against 64-bit sums is unchanged
-// (2.6e-7 and 8.9e-7 at N = 64).
+// N = 256 with 5 x 10^4 views 398 -> 100 ms.  The relative error against 64-bit sums at N = 64 went from
+// 2.5e-7 to 2.3e-7 and from 9.05e-7 to 9.00e-7 (means of four seeds; the deconvolution by the transform
+// of the FP32 window polynomials is part of it).
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -144,6 +145,11 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
     // A lane's part of the 16 x CJ x 8 footprint: columns (axis 1, axis 2) = (NJ e + n, kk), rows
     // (axis 0) 4 q + r of accumulator register r; as an operand, point q of the four, row lane & 15.
     const int q = lane >> 4, e = (lane >> 3) & 1, kk = lane & 7;
+    // A chunk's sums.  The kernel's terms are all positive, and a chain of roundings over 64 of them
+    // raised its error at N = 64 from 2.6e-7 to 2.9e-7: at W <= 7 each round sums on its own (16 terms
+    // in a chain) and is added to them (140.0 -> 141.5 ms at N = 256).  A*b's terms have both signs: its
+    // error is the same either way (8.9e-7 at N = 64), and the second set of registers cost 7%.  At
+    // W = 8 there are no registers for it, and the chunks are half as long.
     struct Sums {
         pts::f4 acc[NC][NJ];
     };
@@ -161,6 +167,18 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
     auto round = [&](Sums& x, int cnt, int) {
         // the operands of KB steps (four points each) are read together, then used
         constexpr int KB = NJ == 4 ? 4 : 1;
+        constexpr bool APART = KB == 4 && !CPLX;
+        pts::f4 part[NC][APART ? NJ : 1];
+        auto& acc = [&]() -> auto& {
+            if constexpr (APART) return part;
+            else return x.acc;
+        }();
+        if constexpr (APART) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int n = 0; n < NJ; ++n) acc[c][n] = pts::f4{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
         for (int kb = 0; kb < 4; kb += KB) {
             float w0[KB], v0[KB], v1[KB], w2[KB], w1[KB][NJ];
@@ -191,9 +209,15 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
                     const float w12 = w1[j][n] * w2[j];
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
-                        x.acc[c][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[c], w12, x.acc[c][n], 0, 0, 0);
+                        acc[c][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[c], w12, acc[c][n], 0, 0, 0);
                 }
             }
+        }
+        if constexpr (APART) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int n = 0; n < NJ; ++n) x.acc[c][n] += part[c][n];
         }
     };
     auto close = [&](const Sums& x, int bin) {
@@ -394,6 +418,7 @@ std::vector<int> points_worklist(int L, TileDims T, int W, int M) {
     const double Rt = 0.5 * std::sqrt((double)T0 * T0 + (double)T1 * T1 + (double)T2 * T2);
     struct Tile { double expect; int t; };
     std::vector<Tile> tiles;
+    tiles.reserve((size_t)n0 * n1 * n2);
     double total = 0.0;
     for (int a = 0; a < n0; ++a)
         for (int b = 0; b < n1; ++b)
@@ -407,20 +432,29 @@ std::vector<int> points_worklist(int L, TileDims T, int W, int M) {
                 total += expect;
             }
     const double chunk = std::max((double)gran, total / SP_ITEMS);
-    struct Item { double w; int t, m0, m1; };
-    std::vector<Item> items;
+    // items by descending work, to the resolution of NBK classes (a counting sort: 2.4 x 10^5 items at
+    // N = 256)
+    constexpr int NBK = 2048;
+    auto parts = [&](const Tile& t) { return std::max(1, (int)std::ceil(t.expect / chunk)); };
+    double wmax = 1.0;
+    for (const Tile& t : tiles) wmax = std::max(wmax, t.expect / parts(t));
+    auto cls = [&](const Tile& t, int nch) { return std::min(NBK - 1, (int)(NBK * (1.0 - t.expect / nch / wmax))); };
+    auto step = [&](int nch) { return ((M + nch - 1) / nch + gran - 1) / gran * gran; };
+    std::vector<size_t> at(NBK + 1, 0);
     for (const Tile& t : tiles) {
-        const int nch = std::max(1, (int)std::ceil(t.expect / chunk));
-        const int per = ((M + nch - 1) / nch + gran - 1) / gran * gran;
-        for (int k = 0; k < nch; ++k) {
-            const int m0 = k * per, m1 = std::min(M, m0 + per);
-            if (m0 < m1) items.push_back({t.expect / nch, t.t, m0, m1});
+        const int nch = parts(t), per = step(nch);
+        at[cls(t, nch) + 1] += (size_t)((M + per - 1) / per);
+    }
+    for (int i = 0; i < NBK; ++i) at[i + 1] += at[i];
+    std::vector<int> out(4 * at[NBK]);
+    for (const Tile& t : tiles) {
+        const int nch = parts(t), per = step(nch);
+        size_t& i = at[cls(t, nch)];
+        for (int m0 = 0; m0 < M; m0 += per, ++i) {
+            int* o = &out[4 * i];
+            o[0] = t.t; o[1] = m0; o[2] = std::min(M, m0 + per); o[3] = 0;
         }
     }
-    std::stable_sort(items.begin(), items.end(), [](const Item& u, const Item& v) { return u.w > v.w; });
-    std::vector<int> out;
-    out.reserve(items.size() * 4);
-    for (auto& it : items) { out.push_back(it.t); out.push_back(it.m0); out.push_back(it.m1); out.push_back(0); }
     return out;
 }
 

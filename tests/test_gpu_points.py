@@ -65,6 +65,23 @@ def test_many_points_per_tile(firm):
     plan.close()
 
 
+@pytest.mark.parametrize("W", [4, 5, 6, 7, 8])
+@pytest.mark.parametrize("N,M", [(32, 3), (8, 2500)])
+def test_projector_with_few_and_many_points_per_tile(firm, W, N, M):
+    """The forward projector's two tile shapes: a few points per tile, and queuefuls of them."""
+    print(f"project W={W} N={N} M={M}", flush=True)
+    R, sh, grp, table = small_geometry(N, M, 400 + W, 3, True)
+    V = np.random.default_rng(W).standard_normal((N, N, N)).astype(np.float32)
+    plan = firm.Plan(N, R, shifts=sh, ctf_group=grp, ctf_table=table, kb_width=W)
+    got = plan.forward_project(torch.as_tensor(V).cuda())
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    some = np.unique(np.linspace(0, M - 1, 12).astype(int))  # the oracle on some of the views
+    ref = ofirm.forward_project(V, R[some], ofirm.ctf_weights(N, M, grp, table)[some]) * ofirm.shift_phase(N, sh[some]).conj()
+    assert rel(got[some], ref) < tol(W)
+    plan.close()
+
+
 def test_a_point_that_is_not_a_number_touches_no_other(firm):
     """A NaN sample drops its own point (the pair k, -k), as the integer conversion always did."""
     N, M = 16, 40

@@ -8,11 +8,11 @@ import math
 import numpy as np
 import pytest
 
-NTH, NW, CHUNK, GROUP, RUN, SURV = 1024, 16, 64, 32768, 64, 96
+NTH, NW, GROUP, RUN, SURV = 1024, 16, 32768, 64, 96
 LDS = 160 * 1024 - 640  # 132 row starts of the disk are the kernels' own
 # (lattice step, bins along axis 0, bound on P1, row pitch, bytes per cell, floats per value)
 KINDS = {"ker": (4, 1, 22, 22, 8, 1), "atb": (2, 1, 14, 18, 16, 2), "atb8": (2, 1, 16, 18, 16, 2),
-         "prj": (2, 1, 18, 18, 8, 2)}
+         "prj": (2, 1, 18, 18, 8, 2), "prjw": (2, 1, 22, 22, 8, 2)}
 
 
 class Tile:
@@ -21,6 +21,7 @@ class Tile:
             kind = "atb8"
         self.S, NB0, P1MAX, self.RP, CELL, self.NV = KINDS[kind]
         self.W = W
+        self.CHUNK = 32 if W == 8 else 64
         self.NJ = 8 if W == 8 else 4
         self.CJ = 2 * self.NJ
         self.B = (17 - W, self.CJ + 1 - W, 9 - W)
@@ -34,7 +35,7 @@ class Tile:
         self.WAVE = self.LEAD + 16 * self.S0 + 16 * self.SB
         fixed = (self.P[0] * self.P[1] * self.RP * CELL + NW * self.WAVE * 4 + NW * SURV * 2 + GROUP // RUN * 2 +
                  self.nbins * 4 + 64)
-        per = lambda q: q * (20 + 4 * self.NV) + (q // CHUNK + self.nbins) * 4  # noqa: E731
+        per = lambda q: q * (20 + 4 * self.NV) + (q // self.CHUNK + self.nbins) * 4  # noqa: E731
         q = 4096
         while q > 1024 and fixed + per(q) > LDS:
             q -= 256
@@ -43,7 +44,7 @@ class Tile:
         self.ROWS, self.CMAX = self.DIAG // self.S + 1, self.DIAG // self.S + 2
 
 
-ALL = [(k, W) for k in ("ker", "atb", "prj") for W in range(4, 9)]
+ALL = [(k, W) for k in ("ker", "atb", "prj", "prjw") for W in range(4, 9)]
 
 
 @pytest.mark.parametrize("kind,W", ALL)
@@ -52,8 +53,8 @@ def test_budgets_and_footprints(kind, W):
     assert t.lds <= LDS and all(n >= 1 for n in t.NB) and t.P[1] <= t.P1MAX and t.P[2] <= t.RP and t.nbins <= 192
     # a chunk-table entry: bin above bit 20, start in 13 bits, count in 7; the packed scan of
     # (chunks << 16) | points; at most one chunk per CHUNK points and one more per bin
-    assert t.QCAP <= 8191 and CHUNK < 128 and t.nbins < 2048
-    assert t.QCAP // CHUNK + t.nbins < 32768 and t.QCAP < 65536
+    assert t.QCAP <= 8191 and t.CHUNK < 128 and t.nbins < 2048
+    assert t.QCAP // t.CHUNK + t.nbins < 32768 and t.QCAP < 65536
     assert 64 * t.CMAX <= t.QCAP  # one step of a wavefront always fits an empty queue
     # a queue entry: 15 bits of view, k1 <= N/2 <= 128 in 8, k2 + 256 in 9; views collected per step
     assert GROUP <= 1 << 15 and GROUP // RUN * RUN == GROUP and SURV - RUN + RUN <= SURV
