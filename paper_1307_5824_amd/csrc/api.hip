@@ -717,6 +717,10 @@ firm_status firm_precond_apply(firm_plan p, const float* d, const float* r, floa
 
 firm_status firm_images_to_slices(firm_plan p, const float* images, void* b) {
     if (!p || !images || !b) return firm_fail(p, FIRM_ERR_ARG, "null argument");
+    if (p->N <= 128) {
+        FIRM_HIP(p, images_slices(p, images, (float2*)b));
+        return FIRM_OK;
+    }
     const size_t per = (size_t)p->N * p->QPn * sizeof(float2);
     const int G = (int)std::max<size_t>(1, std::min<size_t>((size_t)p->M, (size_t(1) << 30) / per));
     firm_status s = ensure_ws(p, &p->img_ws, &p->img_ws_bytes, (size_t)G * per);

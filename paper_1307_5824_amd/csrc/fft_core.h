@@ -127,10 +127,10 @@ struct Pen {
     }
 };
 
-template <int L, int C, bool JF, int R, int NS, class V>
+// P: the layout of the exchange buffer (idx of element e of pencil c); TWN: the twiddle table's length.
+template <class P, int L, int R, int NS, int TWN, class V>
 __device__ __forceinline__ void reg_stage(V (&v)[8], V* lds, const V* __restrict__ tw, typename CxT<V>::S sg,
                                           int c, int j) {
-    using P = Pen<L, C, JF>;
     constexpr int NB = 8 / R;
     constexpr bool FIRST = (NS == 1);
     constexpr bool LAST = (NS * R == L);
@@ -149,7 +149,7 @@ __device__ __forceinline__ void reg_stage(V (&v)[8], V* lds, const V* __restrict
         if (NS > 1) {
 #pragma unroll
             for (int s = 1; s < R; ++s) {
-                V t = tw[(s * k) * (FIRM_TWN / (NS * R))];
+                V t = tw[(s * k) * (TWN / (NS * R))];
                 t.y *= -sg;  // table holds exp(-2 pi i m / T); sg = +1 conjugates
                 w[s] = c_mul(w[s], t);
             }
@@ -180,14 +180,14 @@ constexpr int first_radix(int L) {
     return r;
 }
 
-template <int L, int C, bool JF, int NS, class V>
+template <class P, int L, int NS, int TWN, class V>
 __device__ __forceinline__ void reg_stages(V (&v)[8], V* lds, const V* __restrict__ tw, typename CxT<V>::S sg,
                                            int c, int j) {
     if constexpr (NS < L) {
         // the radix-2 or radix-4 stage (lengths not a power of 8) goes first
         constexpr int R = NS == 1 ? first_radix(L) : 8;
-        reg_stage<L, C, JF, R, NS, V>(v, lds, tw, sg, c, j);
-        reg_stages<L, C, JF, NS * R, V>(v, lds, tw, sg, c, j);
+        reg_stage<P, L, R, NS, TWN, V>(v, lds, tw, sg, c, j);
+        reg_stages<P, L, NS * R, TWN, V>(v, lds, tw, sg, c, j);
     }
 }
 
@@ -196,7 +196,7 @@ __device__ __forceinline__ void reg_stages(V (&v)[8], V* lds, const V* __restric
 template <int L, int C, bool JF, class V>
 __device__ __forceinline__ void fft_reg(V (&v)[8], V* lds, const V* __restrict__ tw, typename CxT<V>::S sg) {
     using P = Pen<L, C, JF>;
-    reg_stages<L, C, JF, 1, V>(v, lds, tw, sg, P::c(), P::j());
+    reg_stages<P, L, 1, FIRM_TWN, V>(v, lds, tw, sg, P::c(), P::j());
 }
 
 // pencils per workgroup for each length (threads = C * L / 8)

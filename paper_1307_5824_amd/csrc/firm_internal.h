@@ -177,6 +177,7 @@ firm_status ensure_fp64(firm_plan p);  // api.hip: FP64 buffers and khat64
 hipError_t forward_project(firm_plan p, const float* V, float2* b);
 
 // ---- images.hip ----
+hipError_t images_slices(firm_plan p, const float* img, float2* b);  // N <= 128, one kernel
 hipError_t images_gather(firm_plan p, const float2* spec, int G, int m0, float2* b);
 hipError_t synth_images(firm_plan p, int B, const double* blobs_dev, double snr, uint64_t seed, float* img,
                         double* partials, int64_t npart);

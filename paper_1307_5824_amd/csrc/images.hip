@@ -16,6 +16,7 @@
 // (m, pixel, 0, 2), sigma^2 = mean clean pixel power / SNR.
 #include <cmath>
 
+#include "fft_core.h"
 #include "firm_internal.h"
 #include "philox.h"
 
@@ -25,23 +26,144 @@
 
 namespace {
 
-// One image row of one disk row per block: block (g, r) writes the points (k1, k2) of row
-// r = k1 + N/2 of image g of the batch.
+// The disk point (k1, k2) from an image's spectrum: get(q1, q1m, k2) gives X(q1, k2) for 0 <= k2 <= N/2,
+// q1m = -q1 mod N; X(k1, -k2) = conj X(-k1, k2).
+template <class F>
+__device__ __forceinline__ float2 disk_value(int N, int k1, int k2, F&& get) {
+    const int q1 = (k1 + N) & (N - 1), q1m = (N - q1) & (N - 1);
+    float2 v = k2 >= 0 ? get(q1, q1m, k2) : get(q1m, q1, -k2);
+    if (k2 < 0) v.y = -v.y;
+    if ((k1 + k2) & 1) { v.x = -v.x; v.y = -v.y; }
+    return v;
+}
+
+// Gather of the disk points from half spectra in HBM (N = 256): a wavefront per row k1 of an image.
 __global__ void __launch_bounds__(IMG_THREADS) k_img_gather(const float2* __restrict__ spec, int N, int QPn, int P,
                                                            const int* __restrict__ rowstart, int m0,
                                                            float2* __restrict__ b) {
-    const int r = blockIdx.x % (N + 1), g = blockIdx.x / (N + 1);
-    const int k1 = r - N / 2;
-    const int kmax = (int)floor(sqrt((double)(N * N / 4 - k1 * k1)) + 1e-9);
+    const int g = blockIdx.x, lane = threadIdx.x & 63;
     const float2* X = spec + (int64_t)g * N * QPn;
-    const int q1 = (k1 + N) % N, q1m = (N - q1) % N;
-    float2* out = b + (int64_t)(m0 + g) * P + rowstart[r];
-    for (int k2 = -kmax + (int)threadIdx.x; k2 <= kmax; k2 += IMG_THREADS) {
-        float2 v = k2 >= 0 ? X[(int64_t)q1 * QPn + k2] : X[(int64_t)q1m * QPn - k2];
-        if (k2 < 0) v.y = -v.y;
-        if ((k1 + k2) & 1) { v.x = -v.x; v.y = -v.y; }
-        out[k2] = v;
+    float2* out = b + (int64_t)(m0 + g) * P;
+    for (int r = threadIdx.x >> 6; r <= N; r += IMG_THREADS / 64) {
+        const int k1 = r - N / 2, left = N * N / 4 - k1 * k1;
+        int kmax = (int)__builtin_amdgcn_sqrtf((float)left);
+        kmax += (kmax + 1) * (kmax + 1) <= left ? 1 : 0;
+        kmax -= kmax * kmax > left ? 1 : 0;
+        for (int k2 = -kmax + lane; k2 <= kmax; k2 += 64)
+            out[rowstart[r] + k2] = disk_value(N, k1, k2, [&](int q1, int, int k) { return X[(int64_t)q1 * QPn + k]; });
     }
+}
+
+// Step 1 of N <= 128 in one kernel: a workgroup holds one image (1,024 threads at N = 128) or, below
+// N = 64, as many as 256 threads transform (16 at N = 16) in LDS, N rows of N/2 columns each, from
+// the pixels to the disk points; HBM moves the pixels and the slices only, 168 KB per image at N = 128
+// instead of 660 (half spectra written and read between the row transforms, the column transforms
+// and the gather).  Rows in pairs, as one complex
+// pencil; the columns q2 = 0 and N/2 of a real image are both real before the column transforms, so
+// they share one complex column.  The transforms exchange in place: a pencil's exchange buffer
+// is its own two rows (9 slots of 8, against bank conflicts), then its own column.  73,728 bytes of LDS
+// and the N twiddles (N = 128) leave room for two workgroups per CU, whose loads, transforms and stores
+// overlap.  N = 128, 10,007 images: 1,630 -> 430 us, 3.9 TB/s (a large copy reaches 4.8); N = 64, 20,000:
+// 1,100 -> 264 us; N = 8, 40,000: 224 -> 21 us.
+template <int N>
+struct ImgTile {
+    static constexpr int H = N / 2, PITCH = H + H / 8;  // complex columns, and the pitch of a row
+    static constexpr int T = N / 8, NT = H * T;         // threads per pencil, per image
+    static constexpr int NTH = NT > 256 ? NT : 256;     // threads per workgroup
+    static constexpr int IPB = NTH / NT;                // images per workgroup
+    struct Rows {  // pencil c: rows 2c and 2c + 1
+        static __device__ __forceinline__ int idx(int e, int c) { return 2 * c * PITCH + e + (e >> 3); }
+    };
+    struct Cols {
+        static __device__ __forceinline__ int idx(int e, int c) { return e * PITCH + c; }
+    };
+};
+
+template <int N>
+__global__ void __launch_bounds__(ImgTile<N>::NTH, 8) k_img_slices(const float* __restrict__ img, int M, int P,
+                                                       const int* __restrict__ rowstart, const float2* __restrict__ tw,
+                                                       float2* __restrict__ b) {
+    using I = ImgTile<N>;
+    constexpr int H = I::H, T = I::T;
+    __shared__ float2 slab[I::IPB * N * I::PITCH];
+    __shared__ float2 twl[N];  // exp(-2 pi i m / N)
+    const int tid = threadIdx.x;
+    if (tid < N) twl[tid] = tw[tid * (FIRM_TWN / N)];
+    const int li = tid % I::NT;
+    const int m = blockIdx.x * I::IPB + tid / I::NT;
+    const bool live = m < M;
+    const float* x = img + (int64_t)(live ? m : M - 1) * N * N;
+    float2* s = slab + tid / I::NT * (N * I::PITCH);
+    float2 v[8];
+    {
+        const int c = li / T, j = li % T;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int e = j + t * T;
+            v[t] = make_float2(__builtin_nontemporal_load(x + (2 * c) * N + e),
+                               __builtin_nontemporal_load(x + (2 * c + 1) * N + e));
+        }
+        __syncthreads();  // the twiddles are in place
+        reg_stages<typename I::Rows, N, 1, N>(v, s, twl, -1.f, c, j);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) s[I::Rows::idx(j + t * T, c)] = v[t];
+        __syncthreads();
+        float2 xa[4], xb[4];  // spectra of the rows 2c and 2c + 1 at q = j + t T < N/2
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int q = j + t * T;
+            const float2 Z = s[I::Rows::idx(q, c)], Zm = s[I::Rows::idx(q == 0 ? H : N - q, c)];
+            if (q == 0) {  // q = 0 and N/2 (Zm), real for each row: the shared column
+                xa[t] = make_float2(Z.x, Zm.x);
+                xb[t] = make_float2(Z.y, Zm.y);
+            } else {
+                xa[t] = make_float2(0.5f * (Z.x + Zm.x), 0.5f * (Z.y - Zm.y));
+                xb[t] = make_float2(0.5f * (Z.y + Zm.y), -0.5f * (Z.x - Zm.x));
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            s[(2 * c) * I::PITCH + j + t * T] = xa[t];
+            s[(2 * c + 1) * I::PITCH + j + t * T] = xb[t];
+        }
+        __syncthreads();
+    }
+    {
+        const int c = li % H, j = li / H;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = s[I::Cols::idx(j + t * T, c)];
+        reg_stages<typename I::Cols, N, 1, N>(v, s, twl, -1.f, c, j);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) s[I::Cols::idx(j + t * T, c)] = v[t];
+        __syncthreads();
+    }
+    // the images' disks: the threads take the points of the (N + 1)^2 squares around them in order
+    constexpr int SQ = (N + 1) * (N + 1);
+    for (int i = tid; i < I::IPB * SQ; i += I::NTH) {
+        const int g = i / SQ, r = i % SQ / (N + 1), k1 = r - N / 2, k2 = i % (N + 1) - N / 2;
+        const int mg = blockIdx.x * I::IPB + g;
+        if (mg >= M) break;
+        if (4 * (k1 * k1 + k2 * k2) > N * N) continue;
+        const float2* X = slab + g * (N * I::PITCH);
+        b[(int64_t)mg * P + rowstart[r] + k2] = disk_value(N, k1, k2, [&](int q1, int q1m, int k) {
+            const float2 a = X[q1 * I::PITCH + (k & (H - 1))];
+            if (k & (H - 1)) return a;
+            const float2 c = X[q1m * I::PITCH];  // the shared column: X0 + i X_{N/2}
+            return k == 0 ? make_float2(0.5f * (a.x + c.x), 0.5f * (a.y - c.y))
+                          : make_float2(0.5f * (a.y + c.y), -0.5f * (a.x - c.x));
+        });
+    }
+}
+
+template <int N>
+hipError_t launch_slices(firm_plan p, const float* img, float2* b) {
+    using I = ImgTile<N>;
+    hipLaunchKernelGGL((k_img_slices<N>), dim3((p->M + I::IPB - 1) / I::IPB), dim3(I::NTH), 0, p->stream, img, p->M, p->P,
+                       p->rowstart, p->tw, b);
+    return hipGetLastError();
 }
 
 struct ImgArgs {
@@ -143,11 +265,22 @@ __global__ void __launch_bounds__(256) k_img_noise(ImgArgs a, const double* __re
 
 int64_t synth_images_scratch(int N, int M) { return (int64_t)M * ((N + IMG_ROWS - 1) / IMG_ROWS) + 1025; }
 
+// Slices of all images in one kernel; N <= 128.
+hipError_t images_slices(firm_plan p, const float* img, float2* b) {
+    switch (p->N) {
+        case 8: return launch_slices<8>(p, img, b);
+        case 16: return launch_slices<16>(p, img, b);
+        case 32: return launch_slices<32>(p, img, b);
+        case 64: return launch_slices<64>(p, img, b);
+        case 128: return launch_slices<128>(p, img, b);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 // b rows m0 .. m0 + G - 1 from the half spectra of G images.
 hipError_t images_gather(firm_plan p, const float2* spec, int G, int m0, float2* b) {
-    const int64_t blocks = (int64_t)G * (p->N + 1);
-    hipLaunchKernelGGL(k_img_gather, dim3((unsigned)blocks), dim3(IMG_THREADS), 0, p->stream, spec, p->N, p->QPn, p->P,
-                       p->rowstart, m0, b);
+    hipLaunchKernelGGL(k_img_gather, dim3(G), dim3(IMG_THREADS), 0, p->stream, spec, p->N, p->QPn, p->P, p->rowstart, m0,
+                       b);
     return hipGetLastError();
 }
 
