@@ -411,6 +411,10 @@ __global__ void __launch_bounds__(PZC * N / 8) k_rows_pz(const float2* __restric
     }
 }
 
+template <int L>
+struct SlabCfg {
+    static constexpr int C = 2048 / L, THREADS = 256;  // all of a slab's row pencils at once
+};
 // The Fourier-diagonal preconditioner's outer passes for N <= 64, one workgroup per i1 slab
 // (the N x N slab and its N x (N/2 + 1) half spectrum fit LDS).  FWD: rows along i3 real to
 // half spectrum (two real rows per complex pencil, as k_rows_r2c), then columns along i2
@@ -418,11 +422,11 @@ __global__ void __launch_bounds__(PZC * N / 8) k_rows_pz(const float2* __restric
 // half spectrum to real (as k_rows_c2r), written to z[i1][i2][i3].  Two launches instead of
 // four: at these sizes a launch costs its few microseconds whatever it moves.
 template <int L, bool FWD>
-__global__ void __launch_bounds__(FftThr<L * 16 + 4>::value)
+__global__ void __launch_bounds__(SlabCfg<L>::THREADS)
 k_precond_slab(const float* __restrict__ r, float2* __restrict__ S1, float* __restrict__ z, int QPn,
                const float2* __restrict__ tw, const int* active) {
     using V = float2;
-    constexpr int N = L, H = N / 2 + 1, C = FftCfg<L, V>::C, T = L / 8, NT = FftCfg<L, V>::THREADS;
+    constexpr int N = L, H = N / 2 + 1, C = SlabCfg<L>::C, T = L / 8, NT = SlabCfg<L>::THREADS;
     static_assert(N / 2 <= C, "the row pencils of a slab are one chunk");
     using PR = Pen<L, C, true>;   // rows: lanes along elements
     using PC = Pen<L, C, false>;  // columns: lanes along columns
@@ -1137,7 +1141,7 @@ hipError_t precond_passes(firm_plan p, const float* dhalf, const float* r, float
     hipStream_t st = p->stream;
     if constexpr (L <= 64) {  // slab kernels around the middle pass: 3 launches instead of 5
         if (!z) return hipErrorInvalidValue;
-        constexpr int NT = FftCfg<L, float2>::THREADS;
+        constexpr int NT = SlabCfg<L>::THREADS;
         hipLaunchKernelGGL((k_precond_slab<L, true>), dim3(N), dim3(NT), 0, st, r, p->S1, (float*)nullptr, QPn,
                            p->tw, active);
         RET_IF(hipGetLastError());

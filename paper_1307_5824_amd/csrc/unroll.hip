@@ -53,16 +53,20 @@ __global__ void __launch_bounds__(UT) k_udot(const float* __restrict__ a, const 
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// sc[slot] = sum of the nb partials
-__global__ void __launch_bounds__(UT) k_ufinish(const double* __restrict__ part, int nb, double* sc, int slot) {
+// sc[slot] = s, the sum of the nb partials; then sc[qslot] = sc[nslot] / s (FIN_DIV: alpha) or
+// s / sc[nslot] (FIN_RATIO: beta)
+enum { FIN_SUM = 0, FIN_DIV, FIN_RATIO };
+__global__ void __launch_bounds__(UT) k_ufinish(const double* __restrict__ part, int nb, double* sc, int slot, int fin,
+                                                int qslot, int nslot) {
     double a = 0.0;
     for (int i = threadIdx.x; i < nb; i += UT) a += part[i];
     const double s = block_sum(a);
-    if (threadIdx.x == 0) sc[slot] = s;
+    if (threadIdx.x == 0) {
+        sc[slot] = s;
+        if (fin == FIN_DIV) sc[qslot] = sc[nslot] / s;
+        if (fin == FIN_RATIO) sc[qslot] = s / sc[nslot];
+    }
 }
-
-__global__ void k_ualpha(double* sc, Slots sl, int i) { sc[sl.alpha(i)] = sc[sl.rho(i)] / sc[sl.pi(i)]; }
-__global__ void k_ubeta(double* sc, Slots sl, int i) { sc[sl.beta(i)] = sc[sl.rho(i + 1)] / sc[sl.rho(i)]; }
 
 // x += alpha p, rn = r - alpha q (FP64 arithmetic, FP32 storage)
 __global__ void __launch_bounds__(UT) k_ustep(float* __restrict__ x, const float* __restrict__ p,
@@ -156,9 +160,10 @@ hipError_t pcg_unrolled(firm_plan p, const float* d, const float* probes, int np
         hipError_t e_ = (call);              \
         if (e_ != hipSuccess) return e_;     \
     } while (0)
-    auto dot = [&](const float* a, const float* b, int slot) -> hipError_t {
+    auto dot = [&](const float* a, const float* b, int slot, int fin = FIN_SUM, int qslot = 0,
+                   int nslot = 0) -> hipError_t {
         hipLaunchKernelGGL(k_udot, dim3(nb), dim3(UT), 0, st, a, b, n, part);
-        hipLaunchKernelGGL(k_ufinish, dim3(1), dim3(UT), 0, st, part, nb, sc, slot);
+        hipLaunchKernelGGL(k_ufinish, dim3(1), dim3(UT), 0, st, part, nb, sc, slot, fin, qslot, nslot);
         return hipGetLastError();
     };
     UCK(precond_set(p, d));
@@ -177,12 +182,10 @@ hipError_t pcg_unrolled(firm_plan p, const float* d, const float* probes, int np
             const float* ri = rs + (int64_t)i * n;
             float* rnext = i + 1 < k ? rs + (int64_t)(i + 1) * n : rn;
             UCK(fft_apply_AtA(p, pv, q, lam));
-            UCK(dot(pv, q, sl.pi(i)));
-            hipLaunchKernelGGL(k_ualpha, dim3(1), dim3(1), 0, st, sc, sl, i);
+            UCK(dot(pv, q, sl.pi(i), FIN_DIV, sl.alpha(i), sl.rho(i)));
             hipLaunchKernelGGL(k_ustep, dim3(nb), dim3(UT), 0, st, x, pv, ri, q, rnext, sc, sl.alpha(i), n);
             UCK(fft_precond(p, p->dhalf, rnext, s));
-            UCK(dot(rnext, s, sl.rho(i + 1)));
-            hipLaunchKernelGGL(k_ubeta, dim3(1), dim3(1), 0, st, sc, sl, i);
+            UCK(dot(rnext, s, sl.rho(i + 1), FIN_RATIO, sl.beta(i), sl.rho(i)));
             hipLaunchKernelGGL(k_udir, dim3(nb), dim3(UT), 0, st, pv, s, sc, sl.beta(i), n);
             UCK(hipGetLastError());
         }
