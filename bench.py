@@ -423,20 +423,15 @@ def main():
                 "apply_model_gbs": round(sum(pb) / (sum(pass_ms) / 1e3) / 1e9, 1)}
 
     # gridding rates (unit: a sample point of the half disk; the k = 0 samples are added in closed
-    # form): each point adds W^3 terms to the LDS tile, one 64-bit integer atomic each (the A*b
-    # spread adds its real and imaginary parts in two launches: 2 W^3).  The bound is the LDS
-    # atomic rate: 9.1 conflict-free 64-bit adds per clock per CU (measured), 256 CUs, 2.4 GHz.
-    # The phases include the grids' FFTs, about 1% of them
+    # form): each point adds W^3 products to the grid (2 W^3 for A*b, real and imaginary parts), on
+    # the matrix units.  The phases include the grids' FFTs
     W = 7
     npts = wl.M * (firm.firm_slice_points(N) - 1) // 2
-    atomic_peak = 9.1 * 256 * 2.4e9
     gridding = {}
     for name, ms, per_pt in (("kernel_spread", ph[0], W ** 3), ("backprojection_spread", ph[1], 2 * W ** 3)):
-        ups = npts * per_pt / (ms / 1e3)
         gridding[name] = {"points": npts, "points_per_s": float(f"{npts / (ms / 1e3):.4g}"),
-                          "updates_per_point": per_pt, "updates_per_s": float(f"{ups:.4g}"),
-                          "lds_atomic_peak_per_s": float(f"{atomic_peak:.4g}"),
-                          "lds_atomic_bound_frac": round(ups / atomic_peak, 4)}
+                          "updates_per_point": per_pt,
+                          "updates_per_s": float(f"{npts * per_pt / (ms / 1e3):.4g}")}
 
     out = {
         "metric": "A*A applies/s at N=256; time-to-1e-5 residual, learned-PCG vs plain CG",
