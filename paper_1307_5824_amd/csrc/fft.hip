@@ -514,6 +514,100 @@ k_precond_slab(const float* __restrict__ r, float2* __restrict__ S1, float* __re
     }
 }
 
+// The product's passes on either side of its middle one for N <= 32, a workgroup per slab i1: FWD: rows
+// along i3, N real padded to L = 2N, modes 0..N kept (as k_rows_r2c), columns along i2 padded to L (as
+// k_cols), into the blocked T2; !FWD: columns back, i2 < N kept, rows back, i3 < N kept (as k_rows_c2r).
+// At these sizes a pass costs its launch and the latency of its loads (4 us each whatever it moves), so
+// three launches beat five though only N workgroups run: the N = 32 product 20.4 -> 13.0 us.  From N = 64
+// on the passes (5 to 6 us each there) have work for more than N workgroups, and the five stay.
+template <int L>
+struct ApplySlab {
+    static constexpr int N = L / 2, T = L / 8, H = N + 1;
+    static constexpr int THREADS = (H * T + 63) / 64 * 64, C = THREADS / T;  // all columns, and rows, at once
+    static constexpr int CB = FftCfg<L, float2>::C;                          // block width of T2
+    static_assert(THREADS % T == 0 && C >= H && N / 2 <= C, "the slab's pencils in one turn");
+};
+template <int L, bool FWD>
+__global__ void __launch_bounds__(ApplySlab<L>::THREADS)
+k_apply_slab(const float* __restrict__ x, float2* __restrict__ T2, float* __restrict__ y, int64_t s_group,
+             int64_t s_elem, const float2* __restrict__ tw) {
+    using A = ApplySlab<L>;
+    using V = float2;
+    constexpr int N = A::N, T = A::T, H = A::H, C = A::C;
+    using PR = Pen<L, C, true>;   // rows: lanes along elements
+    using PC = Pen<L, C, false>;  // columns: lanes along columns
+    __shared__ V lds[PR::LDS > PC::LDS ? PR::LDS : PC::LDS];
+    __shared__ V sl[N * H];  // [i2][q3]
+    __shared__ V twl[L];     // exp(-2 pi i m / L)
+    if (threadIdx.x < L) twl[threadIdx.x] = tw[threadIdx.x * (FIRM_TWN / L)];
+    const int i1 = blockIdx.x;
+    const int c = PR::c(), j = PR::j();  // row pencil c = rows (2c, 2c + 1)
+    const bool rv = c < N / 2;
+    const int col = PC::c(), jj = PC::j();
+    const bool cv = col < H;
+    V* t2 = T2 + (int64_t)(col / A::CB) * s_group + (int64_t)i1 * A::CB + col % A::CB;
+    V v[8];
+    if constexpr (FWD) {
+        const int64_t r0 = ((int64_t)i1 * N + 2 * c) * N;
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            v[t] = t < 4 && rv ? mkv<V>(x[r0 + j + t * T], x[r0 + N + j + t * T]) : mkv<V>(0, 0);
+        __syncthreads();  // the twiddles are in place
+        reg_stages<PR, L, 1, L>(v, lds, twl, -1.f, c, j);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) lds[PR::idx(j + t * T, c)] = v[t];
+        __syncthreads();
+        if (rv) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int q = j + t * T;
+                if (q >= H) continue;
+                const V Z = lds[PR::idx(q, c)];
+                const V Zm = lds[PR::idx((L - q) & (L - 1), c)];
+                sl[(2 * c) * H + q] = mkv<V>(0.5f * (Z.x + Zm.x), 0.5f * (Z.y - Zm.y));
+                sl[(2 * c + 1) * H + q] = mkv<V>(0.5f * (Z.y + Zm.y), -0.5f * (Z.x - Zm.x));
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = t < 4 && cv ? sl[(jj + t * T) * H + col] : mkv<V>(0, 0);
+        reg_stages<PC, L, 1, L>(v, lds, twl, -1.f, col, jj);
+        if (cv) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) t2[(jj + t * T) * s_elem] = v[t];
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = cv ? t2[(jj + t * T) * s_elem] : mkv<V>(0, 0);
+        __syncthreads();  // the twiddles are in place
+        reg_stages<PC, L, 1, L>(v, lds, twl, 1.f, col, jj);
+        if (cv) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) sl[(jj + t * T) * H + col] = v[t];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int e = j + t * T;
+            const int m = e <= N ? e : L - e;
+            const V Ya = rv ? sl[(2 * c) * H + m] : mkv<V>(0, 0);
+            const V Yb = rv ? sl[(2 * c + 1) * H + m] : mkv<V>(0, 0);
+            v[t] = e <= N ? mkv<V>(Ya.x - Yb.y, Ya.y + Yb.x)     // Ya + i Yb
+                          : mkv<V>(Ya.x + Yb.y, Yb.x - Ya.y);    // conj Ya + i conj Yb
+        }
+        reg_stages<PR, L, 1, L>(v, lds, twl, 1.f, c, j);
+        if (rv) {
+            const int64_t r0 = ((int64_t)i1 * N + 2 * c) * N;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                y[r0 + j + t * T] = v[t].x;
+                y[r0 + N + j + t * T] = v[t].y;
+            }
+        }
+    }
+}
+
 // Pencil of the middle pass over nouter rows of ncols columns, C pencils per block.  When C
 // does not divide ncols, the ncols % C columns of every row's last, partial group are packed C
 // to a block (pencils of consecutive rows), in the first blocks of the grid (started first:
@@ -1004,6 +1098,18 @@ hipError_t apply_front_pz(firm_plan p, float* pvec, float lam, const double* bet
     }
 }
 
+// C: along i1 for every (q2, q3): forward, times K^ + lam / L^3, inverse, keep i1 < N.
+// With the unnormalised inverse the lam term adds exactly lam x to the cropped output, so
+// that pass E need not read x
+template <int L>
+hipError_t launch_apply_mid(firm_plan p, float lam, const int* active, double* dotp) {
+    constexpr int N = L / 2, C = FftCfg<L, float2>::C;
+    const int64_t ng = (N + 1 + C - 1) / C, sg = (int64_t)N * C;
+    const float kadd = lam / ((float)L * L * L);
+    return launch_mid<L>(p->stream, p->T2, p->khat, L, N + 1, ng * sg, C, N, p->tw, active, sg, kadd,
+                         p->khat_bf16 ? p->khat16 : nullptr, p->khat_bf16 == 1 ? p->shtab : nullptr, dotp);
+}
+
 template <int L>
 hipError_t apply_front_bc(firm_plan p, float lam, const int* active, double* dotp, hipEvent_t* ev) {
     const int N = L / 2, QP = p->QP;
@@ -1016,14 +1122,8 @@ hipError_t apply_front_bc(firm_plan p, float lam, const int* active, double* dot
     arm_pass_events(ev, 1);
     RET_IF((launch_cols<L, false, MAP_FIRST, EPI_STORE>(st, p->T1, p->T2, N, N + 1, (int64_t)N * QP, 1, QP, C, 1,
                                                           se_, N, L, -1.f, p->tw, EpiArgs(), active, -1, sg_)));
-    // C: along i1 for every (q2, q3): forward, times K^ + lam / L^3, inverse, keep i1 < N.
-    // With the unnormalised inverse the lam term adds exactly lam x to the cropped output, so
-    // that pass E need not read x
-    const float kadd = lam / ((float)L * L * L);
     arm_pass_events(ev, 2);
-    RET_IF((launch_mid<L>(st, p->T2, p->khat, L, N + 1, se_, C, N, p->tw, active, sg_, kadd,
-                          p->khat_bf16 ? p->khat16 : nullptr, p->khat_bf16 == 1 ? p->shtab : nullptr, dotp)));
-    return hipSuccess;
+    return launch_apply_mid<L>(p, lam, active, dotp);
 }
 
 template <int L>
@@ -1049,6 +1149,19 @@ hipError_t apply_back(firm_plan p, float* y, const int* active, const CgStep* st
 
 template <int L>
 hipError_t apply_passes(firm_plan p, const float* x, float* y, float lam, hipEvent_t* ev = nullptr) {
+    if constexpr (L <= 64) {
+        if (!ev) {  // the timed form keeps the five passes that it times
+            using A = ApplySlab<L>;
+            const int64_t ng = (A::H + A::CB - 1) / A::CB, sg = (int64_t)A::N * A::CB, se = ng * sg;
+            hipLaunchKernelGGL((k_apply_slab<L, true>), dim3(A::N), dim3(A::THREADS), 0, p->stream, x, p->T2,
+                               (float*)nullptr, sg, se, p->tw);
+            RET_IF(hipGetLastError());
+            RET_IF(launch_apply_mid<L>(p, lam, nullptr, nullptr));
+            hipLaunchKernelGGL((k_apply_slab<L, false>), dim3(A::N), dim3(A::THREADS), 0, p->stream,
+                               (const float*)nullptr, p->T2, y, sg, se, p->tw);
+            return hipGetLastError();
+        }
+    }
     RET_IF(apply_front<L>(p, x, nullptr, lam, nullptr, nullptr, nullptr, ev));
     return apply_back<L>(p, y, nullptr, nullptr, nullptr, ev);
 }
