@@ -1301,15 +1301,22 @@ hipError_t khat_f64(firm_plan p, const double* k64, double2* w1) {
 }
 
 // Forward N^3 real-to-half-spectrum transform: out [N][N][QPn] complex, FFT order, q3 in [0, N/2].
+// Half spectra of na volumes one after the other, in x as in out; one launch of the rows and one of the
+// columns along i2 serve them all (at N = 64 each fills a fraction of the chip for 4 us: the training
+// batch of 8 with 32 steps, 256 pairs, 46.6 -> 43.9 ms).
 template <int L>
-hipError_t fwd_r2c_passes(firm_plan p, const float* x, float2* out) {
+hipError_t fwd_r2c_passes(firm_plan p, const float* x, float2* out, int na) {
     const int N = L, H = N / 2 + 1, QPn = p->QPn;
+    const int64_t vol = (int64_t)N * N * QPn;
     hipStream_t st = p->stream;
-    RET_IF((launch_r2c<L, false, float>(st, x, N * N, N, N, out, QPn, H, -1.f, p->tw)));
-    RET_IF((launch_cols<L, false, MAP_FIRST, EPI_STORE>(st, out, out, N, H, (int64_t)N * QPn, 1, QPn,
+    RET_IF((launch_r2c<L, false, float>(st, x, na * N * N, N, N, out, QPn, H, -1.f, p->tw)));
+    RET_IF((launch_cols<L, false, MAP_FIRST, EPI_STORE>(st, out, out, na * N, H, (int64_t)N * QPn, 1, QPn,
                                                           (int64_t)N * QPn, 1, QPn, N, N, -1.f, p->tw)));
-    return launch_cols<L, false, MAP_FIRST, EPI_STORE>(st, out, out, N, H, QPn, 1, (int64_t)N * QPn, QPn, 1,
-                                                       (int64_t)N * QPn, N, N, -1.f, p->tw);
+    for (int v = 0; v < na; ++v)
+        RET_IF((launch_cols<L, false, MAP_FIRST, EPI_STORE>(st, out + v * vol, out + v * vol, N, H, QPn, 1,
+                                                              (int64_t)N * QPn, QPn, 1, (int64_t)N * QPn, N, N, -1.f,
+                                                              p->tw)));
+    return hipSuccess;
 }
 
 // Forward-projection grid, L = 2N: N^3 real u (array index i, zero-padded to L per axis) ->
@@ -1500,7 +1507,13 @@ hipError_t fft_precond(firm_plan p, const float* dhalf, const float* r, float* z
 }
 
 hipError_t fft_forward_r2c(firm_plan p, const float* x, float2* out) {
-    DISPATCH_L(p->N, fwd_r2c_passes, p, x, out);
+    DISPATCH_L(p->N, fwd_r2c_passes, p, x, out, 1);
+    return hipErrorInvalidValue;
+}
+
+// two volumes one after the other -> their half spectra one after the other
+hipError_t fft_forward_r2c_pair(firm_plan p, const float* x, float2* out) {
+    DISPATCH_L(p->N, fwd_r2c_passes, p, x, out, 2);
     return hipErrorInvalidValue;
 }
 

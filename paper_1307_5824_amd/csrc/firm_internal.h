@@ -123,6 +123,7 @@ int64_t fft_t2_elems(int N, bool dbl);    // complex elements of the blocked T2 
 size_t blocked_spectrum_elems(int L, int nouter, int ncols, bool dbl);
 hipError_t fft_khat_unblock(firm_plan p, float* out);
 hipError_t fft_forward_r2c(firm_plan p, const float* x, float2* out);  // N^3 real -> [N][N][QPn] half spectrum
+hipError_t fft_forward_r2c_pair(firm_plan p, const float* x, float2* out);  // of two adjacent volumes
 hipError_t chan_spectrum(firm_plan p, double lam, float* out);  // fft.hip: Chan spectrum + lam, centred N^3
 hipError_t kernel_features(firm_plan p, float lam_rel, int res, float* feat);
 hipError_t probe_accumulate(firm_plan p, const float2* zh, const float2* uh, float* A, float* B, double* partials,

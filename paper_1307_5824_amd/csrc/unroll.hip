@@ -102,11 +102,11 @@ __global__ void __launch_bounds__(UT) k_uxbar(float* __restrict__ xb, const floa
         xb[i] = (float)(c * u[i]);
 }
 
-// Pbar = alpha_i xbar + beta_i Pbar - alpha_i u (u = T Rbar_{i+1}; Pbar holds Pbar_{i+1});
+// pb = Pbar_i = alpha_i xbar + beta_i Pbar_{i+1} - alpha_i u (u = T Rbar_{i+1}, pbnext = Pbar_{i+1});
 // at the last step Pbar_{k} = Rbar_{k} = 0, so Pbar = alpha xbar
-__global__ void __launch_bounds__(UT) k_upbar(float* __restrict__ pb, const float* __restrict__ xb,
-                                              const float* __restrict__ u, const double* __restrict__ sc, Slots sl,
-                                              int i, int last, int64_t n) {
+__global__ void __launch_bounds__(UT) k_upbar(float* __restrict__ pb, const float* __restrict__ pbnext,
+                                              const float* __restrict__ xb, const float* __restrict__ u,
+                                              const double* __restrict__ sc, Slots sl, int i, int last, int64_t n) {
     const double a = sc[sl.alpha(i)];
     if (last) {
         for (int64_t j = blockIdx.x * (int64_t)UT + threadIdx.x; j < n; j += (int64_t)gridDim.x * UT)
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(UT) k_upbar(float* __restrict__ pb, const floa
     }
     const double bt = sc[sl.beta(i)];
     for (int64_t j = blockIdx.x * (int64_t)UT + threadIdx.x; j < n; j += (int64_t)gridDim.x * UT)
-        pb[j] = (float)(a * xb[j] + bt * pb[j] - a * u[j]);
+        pb[j] = (float)(a * xb[j] + bt * pbnext[j] - a * u[j]);
 }
 
 // y += x
@@ -145,14 +145,13 @@ hipError_t pcg_unrolled(firm_plan p, const float* d, const float* probes, int np
     hipStream_t st = p->stream;
     const int nb = ublocks(n);
     const Slots sl{k};
-    float* rs = ws;                 // r_0 .. r_{k-1}
-    float* x = ws + (int64_t)k * n;
+    float* rs = ws;                 // r_0 .. r_{k-1} and one more; Pbar_i takes the place of r_{i+1}
+    float* x = ws + (int64_t)(k + 1) * n;
     float* pv = x + n;
     float* q = pv + n;              // products (and u = T e)
     float* s = q + n;               // preconditioned residual / P Sbar
     float* rn = s + n;              // r_k, then Rbar
-    float* pb = rn + n;             // Pbar
-    float* acc = pb + n;            // gradient accumulator, centred grid
+    float* acc = rn + n;            // gradient accumulator, centred grid
     float* junk = p->tmp;           // |F Sbar|^2 of the accumulation, unused
     double* part = p->partials3;
 #define UCK(call)                            \
@@ -204,11 +203,13 @@ hipError_t pcg_unrolled(firm_plan p, const float* d, const float* probes, int np
         for (int i = k - 1; i >= 0; --i) {
             const int last = i == k - 1;
             if (!last) UCK(fft_apply_AtA(p, rn, q, lam));  // u = T Rbar_{i+1}
-            hipLaunchKernelGGL(k_upbar, dim3(nb), dim3(UT), 0, st, pb, x, q, sc, sl, i, last, n);
+            const float* ri = rs + (int64_t)i * n;
+            float* pb = rs + (int64_t)(i + 1) * n;  // next to r_i: the two are transformed together
+            hipLaunchKernelGGL(k_upbar, dim3(nb), dim3(UT), 0, st, pb, last ? nullptr : pb + n, x, q, sc, sl, i, last,
+                               n);
             // dL/dd += Re(conj(F Sbar_i) F r_i) (Sbar_i = Pbar_i), accumulated on the centred grid
-            UCK(fft_forward_r2c(p, pb, p->S1));
-            UCK(fft_forward_r2c(p, rs + (int64_t)i * n, p->S2));
-            UCK(probe_accumulate(p, p->S2, p->S1, junk, acc, part, 1024));
+            UCK(fft_forward_r2c_pair(p, ri, p->T2));
+            UCK(probe_accumulate(p, p->T2, p->T2 + (int64_t)p->N * p->N * p->QPn, junk, acc, part, 1024));
             if (i > 0) {  // Rbar_i = Rbar_{i+1} + P Sbar_i (Rbar_0 is not needed)
                 if (last) UCK(fill_zero(rn, n * sizeof(float), st));
                 UCK(fft_precond(p, p->dhalf, pb, s));
