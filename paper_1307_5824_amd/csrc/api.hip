@@ -379,6 +379,14 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
     p->ntiles_ker = (int)(wk.size() / 4);
     p->ntiles_atb = (int)(wa.size() / 4);
     p->ntiles_prj = (int)(wp.size() / 4);
+    auto ranges = [&](const std::vector<int>& w) {  // view ranges of the most split tile
+        int most = 0;
+        for (size_t i = 0; i < w.size(); i += 4)
+            if (w[i + 1] == 0) most = std::max(most, (M + w[i + 2] - 1) / w[i + 2]);
+        return most;
+    };
+    p->units_ker = ranges(wk) >= sp_units_from(N);
+    p->units_atb = ranges(wa) >= sp_units_from(N);
 
     const int64_t n3 = (int64_t)N * N * N;
     const int64_t N2 = 2 * N;
@@ -481,7 +489,9 @@ firm_status ensure_ws(firm_plan p, void** ptr, size_t* have, size_t need) {
 // Workspaces for both gridding pipelines (sized for the larger, the kernel's).
 firm_status ensure_grid_ws(firm_plan p) {
     const size_t N = p->N, L = 4 * N, N2 = 2 * N;
-    const size_t grid = std::max(L * L * L * sizeof(float), N2 * N2 * N2 * sizeof(float2));
+    // the grid, and behind it the integer one where that is used
+    const size_t units = p->units_ker ? L * L * L : (p->units_atb ? 2 * N2 * N2 * N2 : 0);
+    const size_t grid = L * L * L * sizeof(float) + units * sizeof(int64_t);
     const size_t w1 = std::max({L * L * N * sizeof(float2), N2 * N2 * N * sizeof(float2),
                                 N2 * N2 * (size_t)p->QP * sizeof(float2)});
     const size_t w2 = std::max(L * N2 * N * sizeof(float2) + N2 * N2 * N * sizeof(float),
@@ -490,6 +500,12 @@ firm_status ensure_grid_ws(firm_plan p) {
     if ((s = ensure_ws(p, &p->grid, &p->grid_bytes, grid)) != FIRM_OK) return s;
     if ((s = ensure_ws(p, &p->ws1, &p->ws1_bytes, w1)) != FIRM_OK) return s;
     return ensure_ws(p, &p->ws2, &p->ws2_bytes, w2);
+}
+
+// The integer grid behind the floats of the kernel's grid.
+unsigned long long* grid_units(firm_plan p) {
+    const size_t L = 4 * (size_t)p->N;
+    return reinterpret_cast<unsigned long long*>((char*)p->grid + L * L * L * sizeof(float));
 }
 
 // Ker(0) of the current kernel (circulant position 0), for the relative lambda reading.
@@ -569,8 +585,7 @@ firm_status firm_kernel_precompute(firm_plan p) {
     float2* h1 = (float2*)p->ws1;
     float2* h2 = (float2*)p->ws2;
     float* chalf = (float*)((char*)p->ws2 + L * N2 * N * sizeof(float2));
-    FIRM_HIP(p, fill_zero(grid, L * L * L * sizeof(float), p->stream));
-    FIRM_HIP(p, spread_ker(p, grid));
+    FIRM_HIP(p, spread_ker(p, grid, p->units_ker ? grid_units(p) : nullptr));
     FIRM_HIP(p, fft_ker_grid(p, grid, h1, h2, chalf));
     FIRM_HIP(p, kerc_from_half(p, chalf));
     return spectrum_from_kerc(p);
@@ -616,12 +631,10 @@ firm_status firm_backproject(firm_plan p, const void* b, float* atb) {
     if (!p || !b || !atb) return firm_fail(p, FIRM_ERR_ARG, "null argument");
     firm_status s = ensure_grid_ws(p);
     if (s != FIRM_OK) return s;
-    const size_t N = p->N, L = 2 * N;
     float2* grid = (float2*)p->grid;
     float2* j1 = (float2*)p->ws1;
     float2* j2 = (float2*)p->ws2;
-    FIRM_HIP(p, fill_zero(grid, L * L * L * sizeof(float2), p->stream));
-    FIRM_HIP(p, spread_atb(p, (const float2*)b, grid));
+    FIRM_HIP(p, spread_atb(p, (const float2*)b, grid, p->units_atb ? grid_units(p) : nullptr));
     FIRM_HIP(p, atb_k0_term(p, (const float2*)b, p->dscal));
     FIRM_HIP(p, fft_atb_grid(p, grid, j1, j2, atb, p->dscal));
     return FIRM_OK;

@@ -94,6 +94,7 @@ struct firm_plan_s {
     void* ws2 = nullptr; size_t ws2_bytes = 0;
     int* tiles_ker = nullptr; int ntiles_ker = 0;   // work list for the kernel spread
     int* tiles_atb = nullptr; int ntiles_atb = 0;   // work list for the A*b spread
+    bool units_ker = false, units_atb = false;      // these add to an integer grid (see sp_units_from)
     int* tiles_prj = nullptr; int ntiles_prj = 0;   // work list for the forward projector
     bool prj_wide = false;                          // its tiles are the wide ones (few points per tile)
     double* dscal = nullptr;   // small device scratch for the A*b k=0 term
@@ -164,8 +165,9 @@ int fft_apply_cg_partials(firm_plan p);
 
 // ---- spread.hip ----
 hipError_t set_word(int* p, int v, hipStream_t s);  // *p = v on the device
-hipError_t spread_ker(firm_plan p, float* grid);
-hipError_t spread_atb(firm_plan p, const float2* b, float2* grid);
+// the gridded sums in grid; units: scratch for the same sums as 64-bit integers, or null (see sp_units_from)
+hipError_t spread_ker(firm_plan p, float* grid, unsigned long long* units);
+hipError_t spread_atb(firm_plan p, const float2* b, float2* grid, unsigned long long* units);
 hipError_t atb_k0_term(firm_plan p, const float2* b, double* out);
 hipError_t kerc_from_half(firm_plan p, const float* chalf);
 hipError_t kerc_to_centred(firm_plan p, float* out);
@@ -215,6 +217,14 @@ struct TileDims { int t0, t1, t2; };
 std::vector<int> points_worklist(int L, TileDims T, int W, int M);
 std::vector<int> spread_worklist(int N, int W, int M, bool cplx);
 std::vector<int> project_worklist(int N, int W, int M, int64_t P, bool& wide);
+// A tile's views may be split into ranges, each of which adds its sums to the grid (at most 196 of them at N = 8,
+// 79 at N = 16, 27 at N = 32, 8 at N = 64, 3 from N = 128 on), and a cell lies in four tiles or more.  From this
+// many ranges of the most split tile on, the grid is one of 64-bit integers, rounded to FP32 once at the end.
+// N <= 32: any split; the rounding of FP32 adds is the larger part of A*b's error there (W = 8, slices of one
+// volume, against 64 bits: N = 8 with 5 x 10^4 views 5.5e-7 -> 1.1e-7, N = 16 with 2 x 10^4 2.1e-7 -> 1.1e-7), the
+// integers cost 5 us.  N = 64: five ranges, seven of them 1.37e-7 -> 1.27e-7 for 27 us in 1.4 ms, four
+// (the kernel) 2.87e-7 -> 2.86e-7 for 34 us in 1.0 ms.  N = 128 would gain 1.5% of the error for 0.2 ms in 1.6.
+constexpr int sp_units_from(int N) { return N <= 32 ? 2 : 5; }
 constexpr int SP_VRUN = 64;   // views per run of the gridding's view order (one wavefront's)
 void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, std::vector<float>& datb);
 

@@ -13,7 +13,8 @@
 // instruction.  The chunk's FP32 sums (at most 64 terms) then go to the
 // workgroup's LDS tile as 64-bit integers, one atomic per cell and chunk, where one
 // per cell and point was needed without the matrix units; the tile is added to the
-// global grid at the end with one atomic per nonzero cell.  Each point is spread
+// global grid at the end with one atomic per nonzero cell, in FP32 or, where many
+// ranges share a tile, as the 64-bit integers (sp_units_from).  Each point is spread
 // exactly once.
 //
 // LDS float atomics run at a small fraction of the plain read/write rate on this
@@ -44,7 +45,8 @@ struct SpreadArgs {
     pts::Args p;
     const float* table;
     int Q;
-    void* grid;
+    float* grid;
+    unsigned long long* units;  // when set, the grid's sums as 64-bit integers in fixed-point units, instead of grid
     const float2* b;
     const double* shifts;
     const int* rowstart;  // index of (k1, 0) shifted: idx(k1, k2) = rowstart[k1 + N/2] + k2
@@ -71,6 +73,19 @@ __device__ __forceinline__ unsigned long long to_units(float x) {
     return (unsigned long long)__double_as_longlong((double)x + 6755399441055744.0) - 0x4338000000000000ull;
 }
 
+// The fixed-point unit of a gridding: integer units per unit of grid value, and its reciprocal.
+struct Unit {
+    float fxs;
+    double inv;
+};
+__device__ __forceinline__ Unit unit_of(const SpreadArgs& a) {
+    if (!a.fx_bmax) return Unit{a.fxs, a.fx_inv};
+    const float bm = __uint_as_float(*a.fx_bmax);
+    int e = 0;
+    if (bm > 0.f) e = (int)fmin(fmax(floor(log2((double)a.fx_coef / (double)bm)), -100.0), 100.0);
+    return Unit{ldexpf(1.f, e), ldexp(1.0, -e)};
+}
+
 // A point's value in fixed-point units: every term stays below 2^31 for finite data; NaN counts as
 // zero and infinities as 2^32, so that no other point of the bin is touched.
 __device__ __forceinline__ float bounded(float v) {
@@ -86,15 +101,9 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
     __shared__ int rowstart[CPLX ? 132 : 1];  // the disk's rows k1 >= 0 (N <= 256)
 
     const int tid = threadIdx.x, lane = tid & 63;
-    float fxs = a.fxs;
-    double fx_inv = a.fx_inv;
-    if (a.fx_bmax) {
-        const float bm = __uint_as_float(*a.fx_bmax);
-        int e = 0;
-        if (bm > 0.f) e = (int)fmin(fmax(floor(log2((double)a.fx_coef / (double)bm)), -100.0), 100.0);
-        fxs = ldexpf(1.f, e);
-        fx_inv = ldexp(1.0, -e);
-    }
+    const Unit unit = unit_of(a);
+    const float fxs = unit.fxs;
+    const double fx_inv = unit.inv;
     const int N = a.p.N;
     const double inv_n = 1.0 / N;
     if constexpr (CPLX)
@@ -246,14 +255,30 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
             const int g1 = (t1 - T::PADLO + l1 - L / 2) & (L - 1);
             const int g2 = (t2 - T::PADLO + l2 - L / 2) & (L - 1);
             const int64_t gi = ((int64_t)g0 * L + g1) * L + g2;
-            // the integer sum, rounded once to FP32
+            // the integer sum, or that rounded once to FP32
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const long long v = (long long)tile[c][li];
-                if (v) unsafeAtomicAdd(reinterpret_cast<float*>(a.grid) + NC * gi + c, (float)((double)v * fx_inv));
+                if (!v) continue;
+                if (a.units)
+                    __hip_atomic_fetch_add(a.units + NC * gi + c, (unsigned long long)v, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                else
+                    unsafeAtomicAdd(a.grid + NC * gi + c, (float)((double)v * fx_inv));
             }
         }
     });
+}
+
+// grid = units / fxs, each integer sum rounded once to FP32 (n a multiple of 2)
+__global__ void __launch_bounds__(256) k_units_grid(SpreadArgs a, int64_t n) {
+    const double inv = unit_of(a).inv;
+    const longlong2* __restrict__ u = reinterpret_cast<const longlong2*>(a.units);
+    float2* __restrict__ g = reinterpret_cast<float2*>(a.grid);
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n / 2; i += (int64_t)gridDim.x * 256) {
+        const longlong2 v = u[i];
+        g[i] = make_float2((float)((double)v.x * inv), (float)((double)v.y * inv));
+    }
 }
 
 // bits of the largest |component| of n complex values (atomic max on the bits of non-negative
@@ -366,15 +391,18 @@ hipError_t launch_w(firm_plan p, SpreadArgs& a, int nwork) {
     hipError_t e = set_word(p->taken, 0, p->stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_spread<W, CPLX>), dim3(std::min(nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
+    if ((e = hipGetLastError()) != hipSuccess || !a.units) return e;
+    const int64_t n = (int64_t)a.p.L * a.p.L * a.p.L * (CPLX ? 2 : 1);
+    hipLaunchKernelGGL(k_units_grid, dim3(grid_blocks(n / 2)), dim3(256), 0, p->stream, a, n);
     return hipGetLastError();
 }
 
 template <bool CPLX>
-hipError_t launch_spread(firm_plan p, int L, const int* work, int nwork, void* grid, const float2* b, float fxs,
-                         const unsigned* fx_bmax = nullptr, float fx_coef = 0.f) {
+hipError_t launch_spread(firm_plan p, int L, const int* work, int nwork, float* grid, unsigned long long* units,
+                         const float2* b, float fxs, const unsigned* fx_bmax = nullptr, float fx_coef = 0.f) {
     SpreadArgs a;
     a.p = point_args(p, L, work, nwork);
-    a.table = p->table; a.Q = p->Q; a.grid = grid;
+    a.table = p->table; a.Q = p->Q; a.grid = grid; a.units = units;
     a.b = b; a.shifts = p->shiftss; a.rowstart = p->rowstart; a.P = p->P;
     a.fxs = fxs; a.fx_inv = 1.0 / (double)fxs;
     a.fx_bmax = fx_bmax; a.fx_coef = fx_coef;
@@ -479,19 +507,26 @@ hipError_t set_word(int* p, int v, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t spread_ker(firm_plan p, float* grid) {
-    return launch_spread<false>(p, 4 * p->N, p->tiles_ker, p->ntiles_ker, grid, nullptr, p->fx_ker);
+hipError_t spread_ker(firm_plan p, float* grid, unsigned long long* units) {
+    const int64_t L = 4 * p->N, n = L * L * L;
+    hipError_t e = units ? fill_zero(units, n * sizeof(*units), p->stream) : fill_zero(grid, n * sizeof(float), p->stream);
+    if (e != hipSuccess) return e;
+    return launch_spread<false>(p, (int)L, p->tiles_ker, p->ntiles_ker, grid, units, nullptr, p->fx_ker);
 }
 
-hipError_t spread_atb(firm_plan p, const float2* b, float2* grid) {
+hipError_t spread_atb(firm_plan p, const float2* b, float2* grid, unsigned long long* units) {
+    const int64_t L = 2 * p->N, cells = L * L * L;
+    hipError_t e = units ? fill_zero(units, 2 * cells * sizeof(*units), p->stream)
+                         : fill_zero(grid, cells * sizeof(float2), p->stream);
+    if (e != hipSuccess) return e;
     // the fixed-point unit follows from the largest |component| of b, found first
     const int64_t n = (int64_t)p->M * p->P;
     hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, p->stream, p->fx_bmax, 0u);
     hipLaunchKernelGGL(k_absmax, dim3(std::max(1, std::min(grid_blocks(n / 2), 2048))), dim3(256), 0, p->stream,
                        reinterpret_cast<const float4*>(b), n / 2, b + (n / 2) * 2, (int)(n % 2), p->fx_bmax);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_spread<true>(p, 2 * p->N, p->tiles_atb, p->ntiles_atb, grid, b, 1.f, p->fx_bmax, p->fx_atb_coef);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    return launch_spread<true>(p, (int)L, p->tiles_atb, p->ntiles_atb, reinterpret_cast<float*>(grid), units, b, 1.f,
+                               p->fx_bmax, p->fx_atb_coef);
 }
 
 hipError_t atb_k0_term(firm_plan p, const float2* b, double* out) {
