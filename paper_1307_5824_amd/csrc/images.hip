@@ -14,6 +14,7 @@
 // PROJ_CUT sigmas from a pixel row are skipped (their weight is below exp(-PROJ_CUT^2 / 2)).
 // Pixel noise: N(0, sigma^2) per pixel from Philox4x32-10 keyed by the seed, counter
 // (m, pixel, 0, 2), sigma^2 = mean clean pixel power / SNR.
+#include <algorithm>
 #include <cmath>
 
 #include "fft_core.h"
@@ -37,14 +38,15 @@ __device__ __forceinline__ float2 disk_value(int N, int k1, int k2, F&& get) {
     return v;
 }
 
-// Gather of the disk points from half spectra in HBM (N = 256): a wavefront per row k1 of an image.
+// Gather of the disk points from half spectra in HBM (N = 256): a wavefront per row k1 of an image, the
+// image's rows over `parts` workgroups (one image: 98 us with one workgroup, which has 65 rows a wavefront).
 __global__ void __launch_bounds__(IMG_THREADS) k_img_gather(const float2* __restrict__ spec, int N, int QPn, int P,
-                                                           const int* __restrict__ rowstart, int m0,
+                                                           const int* __restrict__ rowstart, int m0, int parts,
                                                            float2* __restrict__ b) {
-    const int g = blockIdx.x, lane = threadIdx.x & 63;
+    const int g = blockIdx.x / parts, part = blockIdx.x % parts, lane = threadIdx.x & 63;
     const float2* X = spec + (int64_t)g * N * QPn;
     float2* out = b + (int64_t)(m0 + g) * P;
-    for (int r = threadIdx.x >> 6; r <= N; r += IMG_THREADS / 64) {
+    for (int r = part * (IMG_THREADS / 64) + (threadIdx.x >> 6); r <= N; r += parts * (IMG_THREADS / 64)) {
         const int k1 = r - N / 2, left = N * N / 4 - k1 * k1;
         int kmax = (int)__builtin_amdgcn_sqrtf((float)left);
         kmax += (kmax + 1) * (kmax + 1) <= left ? 1 : 0;
@@ -279,8 +281,10 @@ hipError_t images_slices(firm_plan p, const float* img, float2* b) {
 
 // b rows m0 .. m0 + G - 1 from the half spectra of G images.
 hipError_t images_gather(firm_plan p, const float2* spec, int G, int m0, float2* b) {
-    hipLaunchKernelGGL(k_img_gather, dim3(G), dim3(IMG_THREADS), 0, p->stream, spec, p->N, p->QPn, p->P, p->rowstart, m0,
-                       b);
+    // eight workgroups per CU, but at least a row for every wavefront
+    const int parts = std::min((p->N + IMG_THREADS / 64) / (IMG_THREADS / 64), (8 * p->ncu + G - 1) / G);
+    hipLaunchKernelGGL(k_img_gather, dim3((unsigned)G * parts), dim3(IMG_THREADS), 0, p->stream, spec, p->N, p->QPn, p->P,
+                       p->rowstart, m0, parts, b);
     return hipGetLastError();
 }
 
