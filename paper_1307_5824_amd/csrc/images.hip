@@ -89,8 +89,10 @@ __global__ void __launch_bounds__(ImgTile<N>::NTH, 8) k_img_slices(const float* 
     constexpr int H = I::H, T = I::T;
     __shared__ float2 slab[I::IPB * N * I::PITCH];
     __shared__ float2 twl[N];  // exp(-2 pi i m / N)
+    __shared__ int row[N + 1];  // the disk's row starts: read from memory at each of 17 points, one image at N = 128 took 14.3 us, now 13.6
     const int tid = threadIdx.x;
     if (tid < N) twl[tid] = tw[tid * (FIRM_TWN / N)];
+    if (tid <= N) row[tid] = rowstart[tid];
     const int li = tid % I::NT;
     const int m = blockIdx.x * I::IPB + tid / I::NT;
     const bool live = m < M;
@@ -150,7 +152,7 @@ __global__ void __launch_bounds__(ImgTile<N>::NTH, 8) k_img_slices(const float* 
         if (mg >= M) break;
         if (4 * (k1 * k1 + k2 * k2) > N * N) continue;
         const float2* X = slab + g * (N * I::PITCH);
-        b[(int64_t)mg * P + rowstart[r] + k2] = disk_value(N, k1, k2, [&](int q1, int q1m, int k) {
+        b[(int64_t)mg * P + row[r] + k2] = disk_value(N, k1, k2, [&](int q1, int q1m, int k) {
             const float2 a = X[q1 * I::PITCH + (k & (H - 1))];
             if (k & (H - 1)) return a;
             const float2 c = X[q1m * I::PITCH];  // the shared column: X0 + i X_{N/2}
