@@ -89,7 +89,7 @@ __global__ void __launch_bounds__(ImgTile<N>::NTH, 8) k_img_slices(const float* 
     constexpr int H = I::H, T = I::T;
     __shared__ float2 slab[I::IPB * N * I::PITCH];
     __shared__ float2 twl[N];  // exp(-2 pi i m / N)
-    __shared__ int row[N + 1];  // the disk's row starts: read from memory at each of 17 points, one image at N = 128 took 14.3 us, now 13.6
+    __shared__ int row[N + 1];  // the disk's row starts (from memory, one image of N = 128 took 14.3 us, now 13.6)
     const int tid = threadIdx.x;
     if (tid < N) twl[tid] = tw[tid * (FIRM_TWN / N)];
     if (tid <= N) row[tid] = rowstart[tid];

@@ -247,26 +247,29 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
         const int t0 = wk.x / nt12 * T::T0, t1 = wk.x / a.p.nt2 % a.p.nt1 * T::T1, t2 = wk.x % a.p.nt2 * T::T2;
         pts::for_points<T>(a.p, s, wk, t0, t1, t2, begin, fetch, value, open, round, close, [](int, int*, int*) {});
         if (!s.any) return;
-        for (int i = tid; i < T::P0 * T::P1 * T::P2; i += pts::NTH) {
-            const int l0 = i / (T::P1 * T::P2), l1 = i / T::P2 % T::P1, l2 = i % T::P2;
-            const int li = (l0 * T::P1 + l1) * T::RP + l2;
-            // grid index = position mod L (a power of 2), position = cell - L/2
-            const int g0 = (t0 - T::PADLO + l0 - L / 2) & (L - 1);
-            const int g1 = (t1 - T::PADLO + l1 - L / 2) & (L - 1);
-            const int g2 = (t2 - T::PADLO + l2 - L / 2) & (L - 1);
-            const int64_t gi = ((int64_t)g0 * L + g1) * L + g2;
-            // the integer sum, or that rounded once to FP32
+        // the tile's sums to the grid, as integers or rounded once to FP32
+        auto flush = [&](auto&& add) {
+            for (int i = tid; i < T::P0 * T::P1 * T::P2; i += pts::NTH) {
+                const int l0 = i / (T::P1 * T::P2), l1 = i / T::P2 % T::P1, l2 = i % T::P2;
+                const int li = (l0 * T::P1 + l1) * T::RP + l2;
+                // grid index = position mod L (a power of 2), position = cell - L/2
+                const int g0 = (t0 - T::PADLO + l0 - L / 2) & (L - 1);
+                const int g1 = (t1 - T::PADLO + l1 - L / 2) & (L - 1);
+                const int g2 = (t2 - T::PADLO + l2 - L / 2) & (L - 1);
+                const int64_t gi = ((int64_t)g0 * L + g1) * L + g2;
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const long long v = (long long)tile[c][li];
-                if (!v) continue;
-                if (a.units)
-                    __hip_atomic_fetch_add(a.units + NC * gi + c, (unsigned long long)v, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                else
-                    unsafeAtomicAdd(a.grid + NC * gi + c, (float)((double)v * fx_inv));
+                for (int c = 0; c < NC; ++c) {
+                    const long long v = (long long)tile[c][li];
+                    if (v) add(NC * gi + c, v);
+                }
             }
-        }
+        };
+        if (a.units)
+            flush([&](int64_t i, long long v) {
+                __hip_atomic_fetch_add(a.units + i, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            });
+        else
+            flush([&](int64_t i, long long v) { unsafeAtomicAdd(a.grid + i, (float)((double)v * fx_inv)); });
     });
 }
 
