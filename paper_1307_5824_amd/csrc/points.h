@@ -286,6 +286,14 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
             if (dmin <= lim && dmax >= -lim) s.live[atomicAdd(&s.nlive, 1)] = (unsigned short)r;
         }
         __syncthreads();
+        const int nlive = __builtin_amdgcn_readfirstlane(s.nlive);
+        // A gather with fewer live runs than wavefronts hands out each run in 2^sh parts of 64 >> sh views, one at
+        // a time: with few views it waits for the one wavefront that finds their points (30 views at N = 16
+        // 49.2 -> 45.4 us).  Not the spreads: their many sparse tiles pay for the idle lanes (Ker at
+        // N = 128 with 30 views 1,156 -> 1,178 us).
+        int sh = 0;
+        if constexpr (T::GATHER)
+            while ((nlive << sh) < NW && sh < 4) ++sh;
         int ent[T::EPT], place[T::EPT];  // the thread's entries of the queueful and their sorted positions
         bool held = false;               // a queueful whose results have not been taken
         int n = 0, ub = 0;  // surviving views collected by the wavefront, first (view, row) not yet queued
@@ -297,17 +305,17 @@ __device__ __forceinline__ void for_points(const Args& a, Lds<T>& s, int4 wk, in
                     // runs until enough views survive to fill the steps below
                     n = 0;
                     ub = 0;
-                    while (n <= SURV - RUN) {
+                    while (sh ? n == 0 : n <= SURV - RUN) {
                         int li = 0;
                         if (lane == 0) li = atomicAdd(&s.next, 1);
                         li = __builtin_amdgcn_readfirstlane(li);
-                        if (li >= s.nlive) break;
-                        const int rel = (int)s.live[li] * RUN + lane;
+                        if (li >= nlive << sh) break;
+                        const int rel = (int)s.live[li >> sh] * RUN + lane;
                         const int64_t m = min(g0 + rel, gend - 1);
                         const float4 ra = a.vrec[2 * m], rb = a.vrec[2 * m + 1];
                         // the plane meets the box, and does so where k1 >= 0 (s k1 is the coordinate along c1)
                         const float nx = ra.y * rb.y - ra.z * rb.x, ny = ra.z * ra.w - ra.x * rb.y, nz = ra.x * rb.x - ra.y * ra.w;
-                        const bool ok = g0 + rel < gend &&
+                        const bool ok = g0 + rel < gend && ((lane << sh) >> 6) == (li & ((1 << sh) - 1)) &&
                                         fabsf(c0 * nx + c1 * ny + c2 * nz) <=
                                             T::H0 * fabsf(nx) + T::H1 * fabsf(ny) + T::H2 * fabsf(nz) + 2e-3f &&
                                         c0 * ra.x + c1 * ra.y + c2 * ra.z + T::H0 * fabsf(ra.x) + T::H1 * fabsf(ra.y) +
