@@ -169,7 +169,8 @@ firm_status firm_apply_AtA(firm_plan plan, const float* x_dev, float* y_dev, dou
  * passes (rows along i3 with padding; columns along i2; the fused multiply pass along i1;
  * inverse along i2; inverse along i3 with crop and lambda x) launched with a pair of HIP
  * events in its own dispatch (hipExtLaunchKernelGGL), and writes the passes' average kernel
- * durations in ms to pass_ms[5] (host).  Synchronises after every product. */
+ * durations in ms to pass_ms[5] (host).  For N <= 32 the first two passes share a launch, and the
+ * last two: each is given half of its launch's duration.  Synchronises after every product. */
 firm_status firm_apply_AtA_timed(firm_plan plan, const float* x_dev, float* y_dev, double lambda, int reps,
                                  float* pass_ms);
 

@@ -1150,20 +1150,22 @@ hipError_t apply_back(firm_plan p, float* y, const int* active, const CgStep* st
 template <int L>
 hipError_t apply_passes(firm_plan p, const float* x, float* y, float lam, hipEvent_t* ev = nullptr) {
     if constexpr (L <= 64) {
-        if (!ev) {  // the timed form keeps the five passes that it times
-            using A = ApplySlab<L>;
-            const int64_t ng = (A::H + A::CB - 1) / A::CB, sg = (int64_t)A::N * A::CB, se = ng * sg;
-            hipLaunchKernelGGL((k_apply_slab<L, true>), dim3(A::N), dim3(A::THREADS), 0, p->stream, x, p->T2,
-                               (float*)nullptr, sg, se, p->tw);
-            RET_IF(hipGetLastError());
-            RET_IF(launch_apply_mid<L>(p, lam, nullptr, nullptr));
-            hipLaunchKernelGGL((k_apply_slab<L, false>), dim3(A::N), dim3(A::THREADS), 0, p->stream,
-                               (const float*)nullptr, p->T2, y, sg, se, p->tw);
-            return hipGetLastError();
-        }
+        using A = ApplySlab<L>;
+        const int64_t ng = (A::H + A::CB - 1) / A::CB, sg = (int64_t)A::N * A::CB, se = ng * sg;
+        arm_pass_events(ev, 0);
+        FIRM_PASS_LAUNCH((k_apply_slab<L, true>), dim3(A::N), dim3(A::THREADS), p->stream, x, p->T2, (float*)nullptr,
+                         sg, se, p->tw);
+        RET_IF(hipGetLastError());
+        arm_pass_events(ev, 2);
+        RET_IF(launch_apply_mid<L>(p, lam, nullptr, nullptr));
+        arm_pass_events(ev, 4);
+        FIRM_PASS_LAUNCH((k_apply_slab<L, false>), dim3(A::N), dim3(A::THREADS), p->stream, (const float*)nullptr, p->T2,
+                         y, sg, se, p->tw);
+        return hipGetLastError();
+    } else {
+        RET_IF(apply_front<L>(p, x, nullptr, lam, nullptr, nullptr, nullptr, ev));
+        return apply_back<L>(p, y, nullptr, nullptr, nullptr, ev);
     }
-    RET_IF(apply_front<L>(p, x, nullptr, lam, nullptr, nullptr, nullptr, ev));
-    return apply_back<L>(p, y, nullptr, nullptr, nullptr, ev);
 }
 
 // FP64 form of the product, for true residuals and the FP64 solver modes: the same
@@ -1421,6 +1423,8 @@ hipError_t apply_events_dispatch(firm_plan p, const float* x, float* y, float la
 }
 }  // namespace
 
+// Events 2 i and 2 i + 1 around pass i; where two passes share a launch (N <= 32: 0 and 1, 3 and 4) it has
+// the outer one's.
 hipError_t fft_apply_AtA_events(firm_plan p, const float* x, float* y, float lam, hipEvent_t* ev) {
     const hipError_t e = apply_events_dispatch(p, x, y, lam, ev);
     tl_pass_ev[0] = tl_pass_ev[1] = nullptr;  // a pass that failed before its launch leaves none armed

@@ -249,7 +249,8 @@ class Plan:
         return out
 
     def apply_AtA_timed(self, x, lam, reps, out=None):
-        """Average ms of the five FFT passes of the product over reps runs."""
+        """Average ms of the five FFT passes of the product over reps runs (N <= 32: passes 0 and 1, and 3 and 4,
+        share a launch and have half of its time each)."""
         self._req(x, self.N ** 3, self._torch.float32)
         out = self._vol(out)
         ms = (ctypes.c_float * 5)()
