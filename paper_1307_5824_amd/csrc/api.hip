@@ -904,8 +904,6 @@ firm_status firm_pcg_unrolled(firm_plan p, const float* d, const float* probes, 
                               (size_t)unrolled_workspace_floats((int)N, k) * sizeof(float));
     if (s == FIRM_OK)
         s = ensure_ws(p, (void**)&p->usc, &p->usc_bytes, (size_t)unrolled_scalar_count(k) * sizeof(double));
-    if (s == FIRM_OK && !p->S2)
-        s = ensure_ws(p, (void**)&p->S2, &p->s2_bytes, (size_t)(N * N * p->QPn) * sizeof(float2));
     if (s != FIRM_OK) return s;
     FIRM_HIP(p, pcg_unrolled(p, d, probes, nprobes, k, (float)lambda_eff(p, lambda), p->uws, p->usc, loss, grad));
     if (!std::isfinite(*loss)) return firm_fail(p, FIRM_ERR_BREAKDOWN, "unrolled PCG: non-finite loss");

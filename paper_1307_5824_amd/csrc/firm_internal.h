@@ -84,7 +84,7 @@ struct firm_plan_s {
     double* host_scal = nullptr; // pinned host mirror
     float* dhalf = nullptr;      // preconditioner diagonal / N^3, FFT order, blocked [q2][q3 group][q1][C]
     float2* S1 = nullptr;        // PCG FFT workspace [N][N][QPn]
-    float2* S2 = nullptr;        // second half-spectrum workspace (probe statistics), on first use
+    float2* S2 = nullptr;        // second half-spectrum workspace (probe statistics, FSC), on first use
     size_t s2_bytes = 0;
     int QPn = 0;
 

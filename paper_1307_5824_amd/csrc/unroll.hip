@@ -137,8 +137,8 @@ int ublocks(int64_t n) { return (int)std::min<int64_t>((n + UT - 1) / UT, UB); }
 int64_t unrolled_workspace_floats(int N, int k) { return (int64_t)(k + 7) * N * N * N; }
 int unrolled_scalar_count(int k) { return Slots{k}.count(); }
 
-// ws: unrolled_workspace_floats(N, k) floats; sc: unrolled_scalar_count(k) doubles; S1, S2 and
-// the product workspaces of the plan.  loss_host: mean loss over the probes; grad (may be null).
+// ws: unrolled_workspace_floats(N, k) floats; sc: unrolled_scalar_count(k) doubles; S1 (the
+// preconditioner's) and the product's workspaces of the plan.  loss_host: mean loss over the probes; grad (may be null).
 hipError_t pcg_unrolled(firm_plan p, const float* d, const float* probes, int nprobes, int k, float lam, float* ws,
                         double* sc, double* loss_host, float* grad) {
     const int64_t n = (int64_t)p->N * p->N * p->N;
