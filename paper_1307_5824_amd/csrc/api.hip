@@ -9,7 +9,6 @@
 
 #include "firm_internal.h"
 
-#define KB_DEG 10
 
 namespace {
 
@@ -96,11 +95,10 @@ void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, 
             poly[j * (D + 1) + k] = (float)y[k];
         }
     }
-    const int NE = D / 2 + 1;
     for (int j = 0; j < (W + 1) / 2; ++j)
         for (int k = 0; k <= D; ++k) {
             const double a = coef[j * (D + 1) + k], b = coef[(W - 1 - j) * (D + 1) + k];
-            p->kb_sym[j * (D + 1) + (k % 2 ? NE + k / 2 : k / 2)] = (float)(0.5 * (k % 2 ? a - b : a + b));
+            p->kb_sym[j * (D + 1) + (k % 2 ? KB_EVEN + k / 2 : k / 2)] = (float)(0.5 * (k % 2 ? a - b : a + b));
         }
     // The transform of the window as the kernels evaluate it, with its FP32 coefficients: their rounding
     // shifts the window's area by up to 2.5e-8 per axis, which the closed form would leave in the results
@@ -127,8 +125,8 @@ void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, 
             const float* c = p->kb_sym + j * (D + 1);
             const double x = gx[i], y = x * x;
             double e = 0.0, o = 0.0;
-            for (int k = NE - 1; k >= 0; --k) e = e * y + (double)c[k];
-            for (int k = D - NE; k >= 0; --k) o = o * y + (double)c[NE + k];
+            for (int k = KB_EVEN - 1; k >= 0; --k) e = e * y + (double)c[k];
+            for (int k = D - KB_EVEN; k >= 0; --k) o = o * y + (double)c[KB_EVEN + k];
             const bool mid = 2 * j + 1 == W;  // the middle cell is its own mirror, and even
             gu.push_back(0.5 * (x + 1.0) - 0.5 * W + j);
             gv.push_back((mid ? 0.5 : 1.0) * gw[i] * (mid ? e : e + x * o));

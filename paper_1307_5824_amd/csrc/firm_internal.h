@@ -11,6 +11,9 @@
 
 #define FIRM_TWN 1024  // twiddle table length: exp(-2 pi i m / 1024), m in [0, 1024)
 
+// degree of the window's polynomials; of one pair of cells KB_EVEN even and KB_DEG + 1 - KB_EVEN odd coefficients
+constexpr int KB_DEG = 10, KB_EVEN = KB_DEG / 2 + 1;
+
 struct firm_plan_s {
     int N = 0, M = 0, G = 0, P = 0, Q = 0;  // Q = N*N/4 + 1 (CTF table width)
     int QP = 0;                              // pitch of the half-spectrum axis (>= N+1)
@@ -44,7 +47,7 @@ struct firm_plan_s {
 
     // Kaiser-Bessel window (host): per pair of mirrored cells a polynomial in 2 f - 1, f in [0, 1] the
     // offset in the cell, 6 even and then 5 odd coefficients
-    float kb_sym[44] = {};
+    float kb_sym[4 * (KB_DEG + 1)] = {};
     float fx_ker = 1.f;        // kernel gridding: integer units per unit (power of 2, terms < 2^31)
     float fx_atb_coef = 0.f;   // A*b gridding: units per unit times the largest |b component| may reach
     int* taken = nullptr;      // device word: work items handed out by the running gridding kernel (inside dscal)

@@ -39,7 +39,6 @@
 
 namespace pts {
 
-constexpr int KB_DEG = 10;
 constexpr int NTH = 1024, NW = NTH / 64;
 constexpr int GROUP = 32768;  // views per group: a queue entry holds 15 bits of view, 8 of k1, 9 of k2
 constexpr int RUN = SP_VRUN;  // views per run (with one box of normals)
@@ -56,7 +55,7 @@ struct Args {
     const int4* work;     // (tile, first view, end view, 0)
     int nwork;
     int* taken;           // items handed out so far (0 at the launch)
-    float sym[44];        // window polynomials, even and odd parts (see weights); by value, so that the
+    float sym[4 * (KB_DEG + 1)];  // window polynomials, even and odd parts (see weights); by value, so that the
                           // coefficients come from scalar registers
 };
 
@@ -152,19 +151,19 @@ __device__ __forceinline__ double left_of(int s, int W, int k1, int k2, double c
 // so cells j and W-1-j share their polynomials: w_j(x) = E_j(x^2) + x O_j(x^2), w_{W-1-j} = E - x O.
 // sym holds per pair the 6 even and then the 5 odd coefficients.
 template <int W>
-__device__ __forceinline__ void weights(const float (&sym)[44], float x, float* w) {
+__device__ __forceinline__ void weights(const float (&sym)[4 * (KB_DEG + 1)], float x, float* w) {
     const float y = x * x;
 #pragma unroll
     for (int j = 0; j < (W + 1) / 2; ++j) {
-        const float* c = sym + 11 * j;
-        float e = c[5], o = c[10];
+        const float* c = sym + (KB_DEG + 1) * j;
+        float e = c[KB_EVEN - 1], o = c[KB_DEG];
 #pragma unroll
-        for (int d = 4; d >= 0; --d) e = fmaf(e, y, c[d]);
+        for (int d = KB_EVEN - 2; d >= 0; --d) e = fmaf(e, y, c[d]);
         if (2 * j + 1 == W) {
             w[j] = e;
         } else {
 #pragma unroll
-            for (int d = 3; d >= 0; --d) o = fmaf(o, y, c[6 + d]);
+            for (int d = KB_DEG - KB_EVEN - 1; d >= 0; --d) o = fmaf(o, y, c[KB_EVEN + d]);
             w[j] = fmaf(o, x, e);
             w[W - 1 - j] = fmaf(-o, x, e);
         }
