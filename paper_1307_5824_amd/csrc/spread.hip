@@ -86,8 +86,9 @@ __device__ __forceinline__ Unit unit_of(const SpreadArgs& a) {
     return Unit{ldexpf(1.f, e), ldexp(1.0, -e)};
 }
 
-// A point's value in fixed-point units: every term stays below 2^31 for finite data; NaN counts as
-// zero and infinities as 2^32, so that no other point of the bin is touched.
+// A point's value in fixed-point units: every term stays below 2^31 for finite data.  NaN counts as
+// zero, so that no other point of the bin is touched.  An infinity counts as 2^32 units; in A*b the unit
+// then follows it (2^100), every finite point rounds to zero and the grid overflows: no voxel is finite.
 __device__ __forceinline__ float bounded(float v) {
     return v == v ? fminf(fmaxf(v, -4294967296.f), 4294967296.f) : 0.f;
 }
