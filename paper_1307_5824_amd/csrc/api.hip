@@ -383,8 +383,8 @@ firm_status firm_plan_create(firm_plan* out, int N, int M, const double* rot, co
             if (w[i + 1] == 0) most = std::max(most, (M + w[i + 2] - 1) / w[i + 2]);
         return most;
     };
-    p->units_ker = ranges(wk) >= sp_units_from(N);
-    p->units_atb = ranges(wa) >= sp_units_from(N);
+    p->units_ker = ranges(wk) >= sp_units_from(N, p->kbw);
+    p->units_atb = ranges(wa) >= sp_units_from(N, p->kbw);
 
     const int64_t n3 = (int64_t)N * N * N;
     const int64_t N2 = 2 * N;

@@ -225,9 +225,10 @@ std::vector<int> project_worklist(int N, int W, int M, int64_t P, bool& wide);
 // many ranges of the most split tile on, the grid is one of 64-bit integers, rounded to FP32 once at the end.
 // N <= 32: any split; the rounding of FP32 adds is the larger part of A*b's error there (W = 8, slices of one
 // volume, against 64 bits: N = 8 with 5 x 10^4 views 5.5e-7 -> 1.1e-7, N = 16 with 2 x 10^4 2.1e-7 -> 1.1e-7), the
-// integers cost 5 us.  N = 64: five ranges, seven of them 1.37e-7 -> 1.27e-7 for 27 us in 1.4 ms, four
-// (the kernel) 2.87e-7 -> 2.86e-7 for 34 us in 1.0 ms.  N = 128 would gain 1.5% of the error for 0.2 ms in 1.6.
-constexpr int sp_units_from(int N) { return N <= 32 ? 2 : 5; }
+// integers cost 5 us.  N = 64: five ranges at W = 8, where they show (1.37e-7 -> 1.27e-7, 27 us in 2.4 ms); at
+// W = 7 they would give 1.51e-7 -> 1.47e-7 for 27 us in 1.38 ms.
+// N = 128 would gain 1.5% of the error for 0.2 ms in 1.6.
+constexpr int sp_units_from(int N, int W) { return N <= 32 ? 2 : (N == 64 && W == 8 ? 5 : 1 << 30); }
 constexpr int SP_VRUN = 64;   // views per run of the gridding's view order (one wavefront's)
 void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, std::vector<float>& datb);
 
