@@ -167,7 +167,6 @@ int fft_apply_cg_step_partials(firm_plan p);
 int fft_apply_cg_partials(firm_plan p);
 
 // ---- spread.hip ----
-hipError_t set_word(int* p, int v, hipStream_t s);  // *p = v on the device
 // the gridded sums in grid; units: scratch for the same sums as 64-bit integers, or null (see sp_units_from)
 hipError_t spread_ker(firm_plan p, float* grid, unsigned long long* units);
 hipError_t spread_atb(firm_plan p, const float2* b, float2* grid, unsigned long long* units);

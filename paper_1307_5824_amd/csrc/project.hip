@@ -70,12 +70,14 @@ __global__ void __launch_bounds__(256) k_fp_prep(const float* __restrict__ V, co
     if (threadIdx.x == 0) partials[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// b(0, m) = h_m(0) sum V; every block forms the same sum of the partials in the same order.
+// b(0, m) = h_m(0) sum V; every block forms the same sum of the partials in the same order.  Also zeroes
+// the gather's item counter.
 __global__ void __launch_bounds__(256) k_fp_k0(const double* __restrict__ partials, int nblk,
                                                const int32_t* __restrict__ group, const float* __restrict__ table,
-                                               int Q, int M, int P, float2* __restrict__ b) {
+                                               int Q, int M, int P, float2* __restrict__ b, int* taken) {
     __shared__ double red[4];
     __shared__ float total;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *taken = 0;
     double acc = 0.0;
     for (int i = threadIdx.x; i < nblk; i += 256) acc += partials[i];
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
@@ -281,8 +283,6 @@ hipError_t launch_w(firm_plan p, ProjArgs& a) {
     using T = ProjTile<W, WIDE>;
     a.p.nt1 = (a.p.L + T::T1) / T::T1;  // starts 0 .. L
     a.p.nt2 = (a.p.L + T::T2) / T::T2;
-    hipError_t e = set_word(p->taken, 0, p->stream);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_project<W, WIDE>), dim3(std::min(a.p.nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
     return hipGetLastError();
 }
@@ -299,7 +299,7 @@ hipError_t forward_project(firm_plan p, const float* V, float2* b) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fp_k0, dim3((p->M + 255) / 256), dim3(256), 0, st, p->partials, nblk, p->group, p->table,
-                       p->Q, p->M, p->P, b);
+                       p->Q, p->M, p->P, b, p->taken);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     float2* X = reinterpret_cast<float2*>(p->grid);
     if ((e = fft_project_grid(p, p->tmp, p->T1, reinterpret_cast<float2*>(p->ws1), X)) != hipSuccess) return e;

@@ -313,7 +313,11 @@ __global__ void __launch_bounds__(256) k_absmax(const float4* __restrict__ b, in
     if (threadIdx.x == 0) atomicMax(out, __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
 }
 
-__global__ void k_set_u32(unsigned* p, unsigned v) { *p = v; }
+// zeroes the item counter, and with it the word of the largest component (A*b)
+__global__ void k_zero_words(int* taken, unsigned* bmax) {
+    *taken = 0;
+    if (bmax) *bmax = 0u;
+}
 
 __global__ void k_fill_zero(float4* p, size_t n4) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x)
@@ -392,10 +396,9 @@ hipError_t launch_w(firm_plan p, SpreadArgs& a, int nwork) {
     using T = SpreadTile<W, CPLX>;
     a.p.nt1 = (a.p.L + T::T1) / T::T1;  // starts 0 .. L
     a.p.nt2 = (a.p.L + T::T2) / T::T2;
-    hipError_t e = set_word(p->taken, 0, p->stream);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_spread<W, CPLX>), dim3(std::min(nwork, p->ncu)), dim3(pts::NTH), 0, p->stream, a);
-    if ((e = hipGetLastError()) != hipSuccess || !a.units) return e;
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.units) return e;
     const int64_t n = (int64_t)a.p.L * a.p.L * a.p.L * (CPLX ? 2 : 1);
     hipLaunchKernelGGL(k_units_grid, dim3(grid_blocks(n / 2)), dim3(256), 0, p->stream, a, n);
     return hipGetLastError();
@@ -506,15 +509,12 @@ hipError_t fill_zero(void* ptr, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t set_word(int* p, int v, hipStream_t s) {
-    hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, s, reinterpret_cast<unsigned*>(p), (unsigned)v);
-    return hipGetLastError();
-}
-
 hipError_t spread_ker(firm_plan p, float* grid, unsigned long long* units) {
     const int64_t L = 4 * p->N, n = L * L * L;
     hipError_t e = units ? fill_zero(units, n * sizeof(*units), p->stream) : fill_zero(grid, n * sizeof(float), p->stream);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(1), 0, p->stream, p->taken, (unsigned*)nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     return launch_spread<false>(p, (int)L, p->tiles_ker, p->ntiles_ker, grid, units, nullptr, p->fx_ker);
 }
 
@@ -525,7 +525,7 @@ hipError_t spread_atb(firm_plan p, const float2* b, float2* grid, unsigned long 
     if (e != hipSuccess) return e;
     // the fixed-point unit follows from the largest |component| of b, found first
     const int64_t n = (int64_t)p->M * p->P;
-    hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(1), 0, p->stream, p->fx_bmax, 0u);
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(1), 0, p->stream, p->taken, p->fx_bmax);
     hipLaunchKernelGGL(k_absmax, dim3(std::max(1, std::min(grid_blocks(n / 2), 2048))), dim3(256), 0, p->stream,
                        reinterpret_cast<const float4*>(b), n / 2, b + (n / 2) * 2, (int)(n % 2), p->fx_bmax);
     if ((e = hipGetLastError()) != hipSuccess) return e;
