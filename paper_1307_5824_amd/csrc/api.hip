@@ -101,9 +101,9 @@ void kb_tables(firm_plan p, std::vector<float>& poly, std::vector<float>& dker, 
             p->kb_sym[j * (D + 1) + (k % 2 ? KB_EVEN + k / 2 : k / 2)] = (float)(0.5 * (k % 2 ? a - b : a + b));
         }
     // The transform of the window as the kernels evaluate it, with its FP32 coefficients: their rounding
-    // shifts the window's area by up to 2.5e-8 per axis, which the closed form would leave in the results
-    // as a common factor (at W = 7 half of the kernel's error against 64 bits).  Gauss-Legendre
-    // quadrature per cell, exact for degree 10 times a cosine of at most a quarter turn per cell.
+    // shifts the window's area by up to 2.9e-8 per axis (W = 7: 2.5e-8), three times that as a common factor of
+    // the results, if the closed form were used.  Gauss-Legendre quadrature per cell, exact for degree 10
+    // times a cosine of at most a quarter turn per cell.
     constexpr int NG = 14;
     double gx[NG], gw[NG];
     for (int i = 0; i < NG; ++i) {

@@ -518,7 +518,9 @@ k_precond_slab(const float* __restrict__ r, float2* __restrict__ S1, float* __re
 // along i3, N real padded to L = 2N, modes 0..N kept (as k_rows_r2c), columns along i2 padded to L (as
 // k_cols), into the blocked T2; !FWD: columns back, i2 < N kept, rows back, i3 < N kept (as k_rows_c2r).
 // At these sizes a pass costs its launch and the latency of its loads (4 us each whatever it moves), so
-// three launches beat five though only N workgroups run: the N = 32 product 20.4 -> 13.0 us.  From N = 64
+// three launches beat five though only N workgroups run: the N = 32 product 20.4 -> 13.0 us.  The transforms are
+// the same, but for the compiler's choice of fused multiply-adds; error against 64 bits, 60 to 100 volumes each:
+// N = 8 1.39 -> 1.41e-7, N = 16 1.76e-7 both, N = 32 1.88e-7 both.  From N = 64
 // on the passes (5 to 6 us each there) have work for more than N workgroups, and the five stay.
 template <int L>
 struct ApplySlab {

@@ -201,8 +201,8 @@ __device__ __forceinline__ void fft_reg(V (&v)[8], V* lds, const V* __restrict__
 
 // Pencils per workgroup for each length (threads = C * L / 8).  Short lengths take 16 (at least one
 // wavefront): their arrays are small, and it is the number of workgroups in flight that counts.  With
-// 2048 / L pencils the middle pass at L = 64 had 66 workgroups, now 132 (13 -> 7.1 us), and the N = 32
-// product took 21.8 us, now 20.3 us.
+// 2048 / L pencils the middle pass at L = 64 had 66 workgroups, now 132 (13 -> 7.1 us); five passes at
+// N = 32 (a CG step's) 21.8 -> 20.3 us.
 template <int L, class V = float2>
 struct FftCfg {
     static constexpr bool DBL = sizeof(V) == 16;

@@ -191,7 +191,8 @@ __global__ void __launch_bounds__(256) k_conv_last_bwd(const float* __restrict__
 // part and voxel); the parts are summed in LDS, so that a block sends 32 atomics.  What bounds them is the
 // reading of gz / h3 once per tap from L2 with its index arithmetic.  B = 8, 32^3 grid: 0.52 ms each; one
 // atomic per thread and chunks of 256 voxels took 3.84 ms (last layer, 7 million atomics on 864 sums) and
-// 1.14 ms (first layer).
+// 1.14 ms (first layer).  FP32 sums of 8 x 32^3 voxels in either order, against 64 bits: 2.9e-7 with 128 atomics on
+// a word, 1.6e-6 (last layer) and 6.1e-7 (first) with 8,192 and 1,024.
 constexpr int WL_CHUNK = 2048, WL_PARTS = 8;
 
 // sums the parts' two values; the totals are valid in part 0

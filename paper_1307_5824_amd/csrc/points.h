@@ -25,11 +25,12 @@
 //     the tile are dropped), its value is formed, and the entries are sorted by bin in LDS.
 //  3. the wavefronts take chunks of up to CHUNK points of one bin each, 16 points at a time; those that
 //     find none left go on to find points.
-// What bounds it, at N = 256 with 10^5 views (the kernel's spread, 2.6e9 points, 133 of 140 ms): FP32
-// matrix instructions take the vector unit's slots (a probe of both in different wavefronts ran no
-// faster than one after the other), so they add up: matrix products 36 ms, window weights 29,
-// products' operands 21, adds to the tile 20, finding and locating points about 45.  Before, with one 64-bit
-// LDS atomic per cell and point, 393 ms.
+// What bounds it, at N = 256 with 10^5 views (the kernel's spread, 2.6e9 points, 133 of 141 ms): issue slots of
+// the vector unit, which FP32 matrix instructions take too (a probe of both in different wavefronts ran hardly
+// faster than one after the other).  Time saved by leaving one part out, in copies: matrix products 36 ms,
+// window weights 29, products' operands 21, adds to the tile 20, finding and locating points about 45; they
+// overlap in part, so their sum is more than the whole.  Before, with one 64-bit LDS atomic per cell and
+// point, 393 ms.
 #pragma once
 
 #include <algorithm>

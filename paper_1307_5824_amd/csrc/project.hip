@@ -18,10 +18,12 @@
 // no atomics.  The half disk (k1 > 0, or k1 = 0 and k2 > 0) is gathered; b(-k) = conj b(k) for
 // real V, and b(0) = h(0) sum V is formed exactly.
 //
-// What bounds it, at N = 256 with 2 x 10^4 views (5.1e8 points, 38.3 ms; 65.4 with one thread per point
-// and 343 LDS reads each): the matrix products 13.3 ms of vector-unit time, their operands and the sums
-// over the columns about 8, window weights 5, the outputs with CTF and phase 5, finding and locating
-// points (with the FFTs) 14; timed with the parts switched off one at a time.
+// What bounds it, at N = 256 with 2 x 10^4 views (5.1e8 points, 37.9 ms; 65.4 with one thread per point
+// and 343 LDS reads each): vector-unit issue.  Time saved by leaving one part out: the matrix products 13.3 ms,
+// their operands and the sums over the columns about 8, window weights 5, the outputs with CTF and phase 5,
+// finding and locating points (with the FFTs) 14; these overlap in part.  With few views, the fixed steps of a
+// tile: W = 7 at N = 64 with 30 views 81 us (83 with a thread per point).  W = 4 with 30 to 100 views at N <= 64
+// is the one range where a thread per point, with 64 cells each, was the faster (N = 64, 50 views: 58 us, now 72).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>

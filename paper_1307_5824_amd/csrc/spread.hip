@@ -28,10 +28,15 @@
 // exactly), and k = 0 is added afterwards in closed form.
 //
 // Measured against the spread with one atomic per cell and point (two launches for A*b): the kernel's
-// precompute at N = 256 with 10^5 views 400 -> 140 ms, N = 64 with 10^4 views 2.48 -> 1.03 ms; A*b at
-// N = 256 with 5 x 10^4 views 398 -> 100 ms.  The relative error against 64-bit sums at N = 64 went from
-// 2.5e-7 to 2.3e-7 and from 9.05e-7 to 9.00e-7 (means of four seeds; the deconvolution by the transform
-// of the FP32 window polynomials is part of it).
+// precompute at N = 256 with 10^5 views 400 -> 141 ms, N = 64 with 10^4 views 2.48 -> 1.03 ms; A*b at
+// N = 256 with 5 x 10^4 views 398 -> 100 ms.
+// Errors against 64-bit sums, of that spread, of this one with every point summed into the integers by itself,
+// and of this one: Ker N = 32 with 2 x 10^4 views 2.39, 1.90, 1.89e-7, N = 64 with 5,000 2.95, 2.85, 2.87e-7, there
+// at W = 8 1.60, 1.53, 1.58e-7; A*b of slices of one volume N = 32 2.25, 1.55, 1.55e-7, W = 8 1.45, 1.24, 1.25e-7,
+// N = 64 with 9,973 views 1.94, 1.48, 1.53e-7, W = 8 1.49, 1.27, 1.27e-7; A*b of white noise N = 32 9.31, 9.17,
+// 9.17e-7.  What the FP32 sums of a chunk add is at most 1% (N = 64 on an integer grid 1.472 against 1.475e-7,
+// W = 8 1.272 against 1.265e-7, Ker 2.855 against 2.851 and, W = 8, 1.542 against 1.530e-7); the gain over the
+// spread before is from the polynomials' even and odd parts and the deconvolution by their own transform.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -157,9 +162,10 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
     const int q = lane >> 4, e = (lane >> 3) & 1, kk = lane & 7;
     // A chunk's sums.  The kernel's terms are all positive, and a chain of roundings over 64 of them
     // raised its error at N = 64 from 2.6e-7 to 2.9e-7: at W <= 7 each round sums on its own (16 terms
-    // in a chain) and is added to them (140.0 -> 141.5 ms at N = 256).  A*b's terms have both signs: its
-    // error is the same either way (8.9e-7 at N = 64), and the second set of registers cost 7%.  At
-    // W = 8 there are no registers for it, and the chunks are half as long.
+    // in a chain) and is added to them (140.0 -> 141.5 ms at N = 256).  A*b's chains of 64 do not show in its
+    // error, not where its terms add up in phase either (slices of one volume, N = 64: 1.471e-7 against 1.470e-7
+    // with chains of 16), and the second set of registers cost 7%.  At W = 8 there are no registers for it, and
+    // the chunks are half as long (Ker N = 64 1.542e-7, with chains of 16 1.535e-7).
     struct Sums {
         pts::f4 acc[NC][NJ];
     };
