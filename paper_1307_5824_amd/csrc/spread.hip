@@ -32,10 +32,10 @@
 // N = 256 with 5 x 10^4 views 398 -> 100 ms.
 // Errors against 64-bit sums, of that spread, of this one with every point summed into the integers by itself,
 // and of this one: Ker N = 32 with 2 x 10^4 views 2.39, 1.90, 1.89e-7, N = 64 with 5,000 2.95, 2.85, 2.87e-7, there
-// at W = 8 1.60, 1.53, 1.58e-7; A*b of slices of one volume N = 32 2.25, 1.55, 1.55e-7, W = 8 1.45, 1.24, 1.25e-7,
+// at W = 8 1.60, 1.53, 1.56e-7; A*b of slices of one volume N = 32 2.25, 1.55, 1.55e-7, W = 8 1.45, 1.24, 1.24e-7,
 // N = 64 with 9,973 views 1.94, 1.48, 1.53e-7, W = 8 1.49, 1.27, 1.27e-7; A*b of white noise N = 32 9.31, 9.17,
-// 9.17e-7.  What the FP32 sums of a chunk add is at most 1% (N = 64 on an integer grid 1.472 against 1.475e-7,
-// W = 8 1.272 against 1.265e-7, Ker 2.855 against 2.851 and, W = 8, 1.542 against 1.530e-7); the gain over the
+// 9.17e-7.  What the FP32 sums of a chunk add is below 1% (N = 64 on an integer grid, Ker 2.855 against 2.851e-7,
+// W = 8 1.535 against 1.530e-7), with views that repeat hundreds of times 5% (Ker at W = 8); the gain over the
 // spread before is from the polynomials' even and odd parts and the deconvolution by their own transform.
 #include <algorithm>
 #include <cmath>
@@ -162,20 +162,35 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
     const int q = lane >> 4, e = (lane >> 3) & 1, kk = lane & 7;
     // A chunk's sums.  The kernel's terms are all positive, and a chain of roundings over 64 of them
     // raised its error at N = 64 from 2.6e-7 to 2.9e-7: at W <= 7 each round sums on its own (16 terms
-    // in a chain) and is added to them (140.0 -> 141.5 ms at N = 256).  A*b's chains of 64 do not show in its
-    // error, not where its terms add up in phase either (slices of one volume, N = 64: 1.471e-7 against 1.470e-7
-    // with chains of 16), and the second set of registers cost 7%.  At W = 8 there are no registers for it, and
-    // the chunks are half as long (Ker N = 64 1.542e-7, with chains of 16 1.535e-7).
+    // in a chain) and is added to them (140.0 -> 141.5 ms at N = 256).  At W = 8, where the window's own error is
+    // smallest and there are no registers for a second set, each round goes to the tile (EACH): with the
+    // chunk's 32 terms in a chain, views that repeat (their terms round alike, again and again) raised Ker's error
+    // from 1.53e-7 to 1.85e-7, now 1.61e-7 (N = 16, 20 views 300 times each), for 6 to 10% of the time (N = 64 with
+    // 10^4 views Ker 1.51 -> 1.64 ms, A*b 2.43 -> 2.68).  A*b's chains of 64 at W <= 7 do not show in its error, not
+    // where its terms add up in phase either (slices of one volume, N = 64: 1.471e-7 against 1.470e-7 with
+    // chains of 16); one view repeated 6,000 times has 8.00e-7 against 7.87e-7.  Chains of 32 cost 4.4%, of 16 13%.
+    constexpr bool EACH = W == 8;
     struct Sums {
-        pts::f4 acc[NC][NJ];
+        pts::f4 acc[EACH ? 1 : NC][EACH ? 1 : NJ];
+        int bin;
     };
-    auto open = [&](int) {
-        Sums x;
+    auto open = [&](int bin) {
+        Sums x{};
+        x.bin = bin;
+        return x;
+    };
+    // the sums of a bin's 16 x CJ x 8 cells to the tile
+    auto add = [&](const pts::f4 (&acc)[NC][NJ], int bin) {
+        const int o0 = bin / (T::NB1 * T::NB2) * T::B0, o1 = bin / T::NB2 % T::NB1 * T::B1, o2 = bin % T::NB2 * T::B2;
+        const int cell = ((o0 + 4 * q) * T::P1 + o1 + NJ * e) * T::RP + o2 + kk;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int n = 0; n < NJ; ++n) x.acc[c][n] = pts::f4{0.f, 0.f, 0.f, 0.f};
-        return x;
+            for (int n = 0; n < NJ; ++n)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    __hip_atomic_fetch_add(&tile[c][cell + (r * T::P1 + n) * T::RP], to_units(acc[c][n][r]),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     const float* const wave = s.wave[tid >> 6];
     const float* const row0 = wave + T::LEAD + q * T::S0 + (lane & 15);
@@ -183,18 +198,12 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
     auto round = [&](Sums& x, int cnt, int) {
         // the operands of KB steps (four points each) are read together, then used
         constexpr int KB = NJ == 4 ? 4 : 1;
-        constexpr bool APART = KB == 4 && !CPLX;
-        pts::f4 part[NC][APART ? NJ : 1];
+        constexpr bool APART = EACH || !CPLX;
+        pts::f4 part[APART ? NC : 1][APART ? NJ : 1] = {};
         auto& acc = [&]() -> auto& {
             if constexpr (APART) return part;
             else return x.acc;
         }();
-        if constexpr (APART) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int n = 0; n < NJ; ++n) acc[c][n] = pts::f4{0.f, 0.f, 0.f, 0.f};
-        }
 #pragma unroll
         for (int kb = 0; kb < 4; kb += KB) {
             float w0[KB], v0[KB], v1[KB], w2[KB], w1[KB][NJ];
@@ -229,7 +238,9 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
                 }
             }
         }
-        if constexpr (APART) {
+        if constexpr (EACH) {
+            add(part, x.bin);
+        } else if constexpr (APART) {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -237,16 +248,7 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
         }
     };
     auto close = [&](const Sums& x, int bin) {
-        const int o0 = bin / (T::NB1 * T::NB2) * T::B0, o1 = bin / T::NB2 % T::NB1 * T::B1, o2 = bin % T::NB2 * T::B2;
-        const int cell = ((o0 + 4 * q) * T::P1 + o1 + NJ * e) * T::RP + o2 + kk;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int n = 0; n < NJ; ++n)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    __hip_atomic_fetch_add(&tile[c][cell + (r * T::P1 + n) * T::RP], to_units(x.acc[c][n][r]),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (!EACH) add(x.acc, bin);
     };
     const int L = a.p.L;
     pts::for_items<T>(a.p, s, [&](int4 wk) {
@@ -255,7 +257,7 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
         pts::for_points<T>(a.p, s, wk, t0, t1, t2, begin, fetch, value, open, round, close, [](int, int*, int*) {});
         if (!s.any) return;
         // the tile's sums to the grid, as integers or rounded once to FP32
-        auto flush = [&](auto&& add) {
+        auto flush = [&](auto&& to_grid) {
             for (int i = tid; i < T::P0 * T::P1 * T::P2; i += pts::NTH) {
                 const int l0 = i / (T::P1 * T::P2), l1 = i / T::P2 % T::P1, l2 = i % T::P2;
                 const int li = (l0 * T::P1 + l1) * T::RP + l2;
@@ -263,20 +265,20 @@ __global__ void __launch_bounds__(pts::NTH, pts::NTH / 256) k_spread(SpreadArgs 
                 const int g0 = (t0 - T::PADLO + l0 - L / 2) & (L - 1);
                 const int g1 = (t1 - T::PADLO + l1 - L / 2) & (L - 1);
                 const int g2 = (t2 - T::PADLO + l2 - L / 2) & (L - 1);
-                const int64_t gi = ((int64_t)g0 * L + g1) * L + g2;
+                const unsigned gi = (unsigned)((g0 * L + g1) * L + g2);  // < 2^30 (L <= 1024)
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     const long long v = (long long)tile[c][li];
-                    if (v) add(NC * gi + c, v);
+                    if (v) to_grid(NC * gi + c, v);
                 }
             }
         };
         if (a.units)
-            flush([&](int64_t i, long long v) {
+            flush([&](unsigned i, long long v) {
                 __hip_atomic_fetch_add(a.units + i, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             });
         else
-            flush([&](int64_t i, long long v) { unsafeAtomicAdd(a.grid + i, (float)((double)v * fx_inv)); });
+            flush([&](unsigned i, long long v) { unsafeAtomicAdd(a.grid + i, (float)((double)v * fx_inv)); });
     });
 }
 

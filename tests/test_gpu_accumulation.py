@@ -12,8 +12,9 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from gpu_common import rel, small_geometry  # noqa: E402
+from gpu_common import ker_to_centred, rel, small_geometry  # noqa: E402
 from oracle import direct  # noqa: E402
+from oracle import firm as ofirm  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +60,18 @@ def test_sums_over_many_views(firm, N, M, W, ker_bound, atb_bound):
     assert ker < ker_bound and atb < atb_bound
     plan.close()
 
+
+def test_repeated_views_at_the_widest_window(firm):
+    """Ker at W = 8 of 20 views repeated 300 times each: the terms of a bin are the same over and over, so the
+    roundings of a long FP32 chain do not average out.  Bound: 1.53e-7, the mean error here of sums that take each point
+    into the integers by itself, and a tenth of it (chains of 16 points 1.61e-7, of
+    32 points 1.85e-7)."""
+    N, errs = 16, []
+    for seed in range(3):
+        R, _, _, _ = small_geometry(N, 20, 800 + seed)
+        plan = firm.Plan(N, np.tile(R, (300, 1, 1)), kb_width=8)
+        plan.kernel_precompute()
+        errs.append(rel(host(plan.kernel_get()), ker_to_centred(300 * ofirm.kernel_direct(N, R).real, N)))
+        plan.close()
+    print(f"repeated views: {errs}", flush=True)
+    assert np.mean(errs) < 1.69e-7
